@@ -8,6 +8,8 @@
 //    and the chain rule to c and alpha
 //  * TV operators, shrinkage and dual update (Eq. 13-14), CG vector updates.
 // All accumulations are FP64 with fixed-order two-stage reductions.
+#include <algorithm>
+
 #include "data.hpp"
 
 namespace fwi {
@@ -37,6 +39,12 @@ constexpr int GT = 64;  // output tile
 constexpr int GK = 16;  // k step
 
 // part[ks][l][i][j] = sum over the split's k range of A[l][i][k] w[k] Bm[l][j][k]
+// NB: blocks of 16 rows and columns of the tile that are in use (4, or fewer
+// when ni and nj are at most 48); the others are neither loaded nor
+// multiplied. Compile-time: with run-time bounds the loads end up behind
+// branches and are waited for one by one (1450 against 740 us for J a and
+// J^H b at 256^2, 8 frequencies, 64 elements).
+template <int NB>
 __global__ void __launch_bounds__(256) k_gemm_nt(const c128* __restrict__ A, long a_ls, int ni,
                                                  const c128* __restrict__ w, const c128* __restrict__ Bm, long b_ls,
                                                  int nj, long n, long kchunk, c128* __restrict__ part, int nf) {
@@ -50,9 +58,9 @@ __global__ void __launch_bounds__(256) k_gemm_nt(const c128* __restrict__ A, lon
   const int lane = t & 63, wv = t >> 6;
   const c128* Al = A + l * a_ls;
   const c128* Bl = Bm + l * b_ls;
-  v4d cr[4], ci[4];
+  v4d cr[NB], ci[NB];
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
+  for (int b = 0; b < NB; ++b) {
     cr[b] = v4d{0.0, 0.0, 0.0, 0.0};
     ci[b] = v4d{0.0, 0.0, 0.0, 0.0};
   }
@@ -63,46 +71,44 @@ __global__ void __launch_bounds__(256) k_gemm_nt(const c128* __restrict__ A, lon
   // (raw loads only: the weight is applied at the LDS store, so no load is
   // waited for before the current tile's products)
   // Loads use clamped indices and are masked at the LDS store, so nothing
-  // waits for them before the current tile's products.
-  constexpr int Q = GT * GK / 256;
-  c128 ra[Q], rb[Q], rw[Q];
-  bool va[Q], vb[Q];
+  // waits for them before the current tile's products. Element q of a thread
+  // is row (t / 16) + 16 q of the tile: row block q.
+  static_assert(GK == 16 && GT == 64 && NB <= 4, "one row block of 16 per load");
+  const int r0 = t / GK, kc0 = t % GK;
+  c128 ra[NB], rb[NB], rw;
   auto fetch = [&](long kb) {
+    const long kc = kb + kc0 < k1 ? kb + kc0 : k1 - 1;
+    rw = w ? w[kc] : mk(1.0, 0.0);
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int e = t + q * 256;
-      const int r = e / GK, c = e % GK;
-      const long k = kb + c;
-      const int ia = ti * GT + r, jb = tj * GT + r;
-      va[q] = k < k1 && ia < ni;
-      vb[q] = k < k1 && jb < nj;
-      const long kc = k < k1 ? k : k1 - 1;
+    for (int q = 0; q < NB; ++q) {
+      const int ia = ti * GT + r0 + 16 * q, jb = tj * GT + r0 + 16 * q;
       ra[q] = Al[(long)(ia < ni ? ia : ni - 1) * n + kc];
       rb[q] = Bl[(long)(jb < nj ? jb : nj - 1) * n + kc];
-      rw[q] = w ? w[kc] : mk(1.0, 0.0);
     }
   };
   if (k0 < k1) fetch(k0);
   for (long kb = k0; kb < k1; kb += GK) {
+    const bool vk = kb + kc0 < k1;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int e = t + q * 256;
-      sa[e / GK][e % GK] = va[q] ? ra[q] * rw[q] : mk(0.0, 0.0);
-      sb[e / GK][e % GK] = vb[q] ? rb[q] : mk(0.0, 0.0);
+    for (int q = 0; q < NB; ++q) {
+      sa[r0 + 16 * q][kc0] = vk && ti * GT + r0 + 16 * q < ni ? ra[q] * rw : mk(0.0, 0.0);
+      sb[r0 + 16 * q][kc0] = vk && tj * GT + r0 + 16 * q < nj ? rb[q] : mk(0.0, 0.0);
     }
     __syncthreads();
     if (kb + GK < k1) fetch(kb + GK);
+    if (NB == 4 || wv < NB) {
 #pragma unroll
-    for (int c = 0; c < GK; c += 4) {
-      // A[i][k] = sa[16 wv + i][c + k], B[k][j] = sb[16 b + j][c + k]
-      const c128 av = sa[16 * wv + (lane & 15)][c + (lane >> 4)];
+      for (int c = 0; c < GK; c += 4) {
+        // A[i][k] = sa[16 wv + i][c + k], B[k][j] = sb[16 b + j][c + k]
+        const c128 av = sa[16 * wv + (lane & 15)][c + (lane >> 4)];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) cmfma(av, sb[16 * b + (lane & 15)][c + (lane >> 4)], cr[b], ci[b]);
+        for (int b = 0; b < NB; ++b) cmfma(av, sb[16 * b + (lane & 15)][c + (lane >> 4)], cr[b], ci[b]);
+      }
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int i = ti * GT + 16 * wv + (lane >> 4) + 4 * v, j = tj * GT + 16 * b + (lane & 15);
@@ -463,8 +469,15 @@ void launch_gemm_nt(int nf, const c128* A, long a_ls, int ni, const c128* w, con
   long kchunk = (n + nks - 1) / nks;
   kchunk = (kchunk + GK - 1) / GK * GK;
   const int tiles = ((ni + GT - 1) / GT) * ((nj + GT - 1) / GT);
-  hipLaunchKernelGGL(k_gemm_nt, dim3(nks, tiles, nf), dim3(256), 0, st, A, a_ls, ni, w, Bm, b_ls, nj, n, kchunk, part,
-                     nf);
+  const int nb = (std::max(ni, nj) + 15) / 16;
+  const dim3 grid(nks, tiles, nf);
+#define FWI_GEMM_NT(NB) \
+  hipLaunchKernelGGL(k_gemm_nt<NB>, grid, dim3(256), 0, st, A, a_ls, ni, w, Bm, b_ls, nj, n, kchunk, part, nf)
+  if (nb == 1) FWI_GEMM_NT(1);
+  else if (nb == 2) FWI_GEMM_NT(2);
+  else if (nb == 3) FWI_GEMM_NT(3);
+  else FWI_GEMM_NT(4);
+#undef FWI_GEMM_NT
   FWI_LAUNCH_CHECK();
   const long tot = (long)nf * ni * nj;
   hipLaunchKernelGGL(k_gemm_nt_final, dim3((unsigned)((tot + 63) / 64)), dim3(1024), 0, st, part, nks, nf, ni, nj,

@@ -1,0 +1,40 @@
+"""The Jacobian products at the edges of their matrix-core tiles: element and
+transmit counts around multiples of 16 and 64, grids around the split sizes,
+against the oracle. Tolerance: FP64 sums of up to n = 4099 terms in another
+order, error below n eps = 1e-12 of the largest output."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fwi_oracle as O
+from paper_2604_15796_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2604_15796_amd import fwi
+    c = fwi.Context(0)
+    yield c
+    c.close()
+
+
+def _err(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+def _dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x)).to(torch.complex128).to(DEV)
+
+
+@pytest.mark.parametrize("nx,nz,ne,nt", [(5, 3, 1, 1), (9, 7, 15, 4), (64, 1, 16, 16), (13, 10, 17, 2), (41, 5, 33, 32),
+                                         (16, 16, 48, 21), (31, 9, 49, 48), (4099 // 11, 11, 65, 64),
+                                         (64, 64, 80, 17)])
+def test_jacobian_products_at_tile_edges_vs_oracle(ctx, nx, nz, ne, nt):
+    p = W.small2d(seed=nx + ne, nx=nx, nz=nz, ne=ne, nf=2)
+    tx, rx = W.random_complex(1, (p.nf, nt, p.n)), W.random_complex(2, (p.nf, ne, p.n))
+    a = W.random_complex(3, (p.n,))
+    ref = O.jacobian_apply_tx(tx, rx, a, p.freqs, p.c0, p.dx, 2)
+    assert _err(ctx.jacobian_apply_tx(p, _dev(tx), _dev(rx), _dev(a)).cpu().numpy(), ref) < 1e-12
