@@ -551,6 +551,7 @@ void plan_solve(Arena& a, const Geo& g, int B, int JM, SolveBufs<T>& s) {
   k.iters = a.take<int>(B);
   k.counters = a.take<int>(4);  // active counts, then the max relative residual: one copy reads both
   k.maxrel = k.counters ? reinterpret_cast<double*>(k.counters + 2) : nullptr;
+  k.arrive = a.take<unsigned long long>(1);
   s.rowpart = a.take<double>((size_t)B * g.nz * g.ny);
   s.U1 = a.take<cplx<T>>((size_t)B * g.u1());
   s.U2 = g.dim == 3 ? a.take<cplx<T>>((size_t)B * g.u2()) : nullptr;
@@ -689,10 +690,16 @@ XUpdate cycle_update(const KrylovState<T>& ks, int first, int steps) {
 template <typename T>
 SolveTotals run_solve(fwi_ctx* c, const Geo& g, const c128* m64, const cplx<T>* mT, const c128* ghat64,
                       const cplx<T>* ghatT, int B, const c128* b64, const int* rhs_freq, c128* x64,
-                      const fwi_solve_opts& o, SolveBufs<T>& s, int nfreq) {
+                      const fwi_solve_opts& o, const SolveBufs<T>& bufs, int nfreq) {
   tl_nfreq = nfreq;
   hipStream_t st = c->stream;
+  SolveBufs<T> s = bufs;
   KrylovState<T>& ks = s.ks;
+  // The kernels write the counts that the host waits for straight to pinned
+  // memory: one slot for the cycle start, two for the steps in turn (step j
+  // is enqueued before the count of step j-1 is read, step j+1 after).
+  int* const h_cycle = c->h_int + 16;
+  int* const h_step[2] = {c->h_int + 32, c->h_int + 36};
   const bool fp32 = std::is_same<T, float>::value;
   const double inner = fp32 ? o.inner_rtol : 0.0;
   const int max_cycles = fp32 ? o.max_refine : (o.max_iter + o.restart - 1) / o.restart + 1;
@@ -720,21 +727,22 @@ SolveTotals run_solve(fwi_ctx* c, const Geo& g, const c128* m64, const cplx<T>* 
       krylov_rows_norm(ks, s.rowpart, g.nz * g.ny, st);
       res.matvecs += B;
     }
+    ks.counters = h_cycle;
+    ks.maxrel = reinterpret_cast<double*>(h_cycle + 2);
     krylov_cycle_init(ks, cyc == 0, o.rtol, inner, st);
-    FWI_HIP(hipMemcpyAsync(c->h_int, ks.counters, 2 * sizeof(int) + sizeof(double), hipMemcpyDeviceToHost, st));
     FWI_HIP(hipEventRecord(c->count_ev, st));
     FWI_HIP(hipEventSynchronize(c->count_ev));
-    std::memcpy(&res.maxrel, c->h_int + 2, sizeof(double));
+    std::memcpy(&res.maxrel, h_cycle + 2, sizeof(double));
     if (!std::isfinite(res.maxrel)) throw Error(FWI_E_NONFINITE, "non-finite residual in the Krylov solve");
-    const int nact = c->h_int[0];
+    const int nact = h_cycle[0];
     tl_active = nact;
     if (nact == 0) break;
     if (cyc >= max_cycles || total >= o.max_iter) {
       res.unconverged = nact;
       break;
     }
-    // The active count after step j-1 is copied asynchronously and read only
-    // once step j is enqueued, so the device does not wait for the host
+    // The active count after step j-1 is read only once step j is enqueued, so
+    // the device does not wait for the host
     // between steps; a step enqueued after every RHS stopped runs fully masked.
     // Once at most half the RHS are left, the host waits for each count
     // before enqueueing the next step instead (a wait costs less than a
@@ -745,6 +753,7 @@ SolveTotals run_solve(fwi_ctx* c, const Geo& g, const c128* m64, const cplx<T>* 
     if (cyc > 0) drv.first_rows();
     for (int j = 0;; ++j) {
       const size_t mark = tl_prof ? tl_prof->mark() : 0;
+      ks.counters = h_step[j & 1];
       drv.tail(j);
       ++total;
       ++steps;
@@ -753,7 +762,7 @@ SolveTotals run_solve(fwi_ctx* c, const Geo& g, const c128* m64, const cplx<T>* 
       if (pending) {
         pending = false;
         FWI_HIP(hipEventSynchronize(c->count_ev));
-        known = c->h_int[8];  // RHS that step j processed
+        known = h_step[(j - 1) & 1][0];  // RHS that step j processed
         tl_active = known;
         if (tl_prof) tl_prof->set_active(mark, known);
         if (known == 0) {
@@ -764,11 +773,10 @@ SolveTotals run_solve(fwi_ctx* c, const Geo& g, const c128* m64, const cplx<T>* 
       }
       if (last) break;
       if ((j + 1) % o.check_every == 0) {
-        FWI_HIP(hipMemcpyAsync(c->h_int + 8, ks.counters, sizeof(int), hipMemcpyDeviceToHost, st));
         FWI_HIP(hipEventRecord(c->count_ev, st));
         if (2 * known <= B) {
           FWI_HIP(hipEventSynchronize(c->count_ev));
-          known = c->h_int[8];
+          known = h_step[j & 1][0];
           tl_active = known;
           if (known == 0) break;
         } else {
@@ -923,11 +931,16 @@ struct Runner {
     const int B = nf * per;
     const cplx<T>* mT = std::is_same<T, float>::value ? (const cplx<T>*)cb.m32 : (const cplx<T>*)cb.m64;
     const cplx<T>* gT = std::is_same<T, float>::value ? (const cplx<T>*)pc.ghat32 : (const cplx<T>*)pc.ghat64;
-    launch_fill_rfreq(B, per, l0, cb.rfreq, c->stream);
+    // element transmits of whole frequencies: the problem's own table
+    const int* rfreq = pc.rhs_freq + (long)l0 * p->ne;
+    if (per != p->ne) {
+      launch_fill_rfreq(B, per, l0, cb.rfreq, c->stream);
+      rfreq = cb.rfreq;
+    }
     // a short batch reuses the planned buffers with a smaller B
     SolveBufs<T> s = sb;
     s.ks.B = B;
-    SolveTotals r = run_solve<T>(c, g, cb.m64, mT, pc.ghat64, gT, B, rhs, cb.rfreq, out, o, s, nf);
+    SolveTotals r = run_solve<T>(c, g, cb.m64, mT, pc.ghat64, gT, B, rhs, rfreq, out, o, s, nf);
     tot.merge(r);
   }
 

@@ -89,15 +89,12 @@ __global__ void __launch_bounds__(KT) k_dots(const cplx<T>* __restrict__ V, long
 // reducing vectors i = w, w + 4, ..., each lane a fixed subset of parts, then
 // a fixed-order wave sum. The classical Gram-Schmidt coefficients
 // coef_i = -h_i * scale_i (the update uses the stored, unnormalised vectors)
-// go to hcoef for the first pass of the next matvec. Zeroes the active count
-// that k_givens accumulates.
+// go to hcoef for the first pass of the next matvec.
 template <typename T, int JM>
 __global__ void __launch_bounds__(KT) k_hsum(int j, int B, const int* __restrict__ active,
                                              const cplx<T>* __restrict__ vscale, const c128* __restrict__ dotp,
-                                             int ndot, c128* __restrict__ H, c128* __restrict__ hcoef,
-                                             int* __restrict__ counters) {
+                                             int ndot, c128* __restrict__ H, c128* __restrict__ hcoef) {
   const int b = blockIdx.x;
-  if (b == 0 && threadIdx.x == 0) counters[0] = 0;
   if (!active[b]) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int i = w; i <= j; i += KT / 64) {
@@ -121,30 +118,59 @@ __global__ void __launch_bounds__(KT) k_hsum(int j, int B, const int* __restrict
 // from its per-row sums, summed by the whole workgroup in a fixed order;
 // previous rotations, new rotation), update the residual estimate and the
 // convergence mask, count the RHS still active.
+// Bound by latency, not by bytes: the column and the earlier rotations are
+// fetched by all threads at once into LDS while the row sums are loaded, so
+// the serial rotations run from LDS (each fetched them from memory in turn
+// before: 4.5 us at 13 columns of 64^2, 9.5 at 20; now 3.8 and 6). The
+// count of active RHS and of workgroups arrived share one 64-bit atomic, so
+// the last workgroup knows the total without a fence and writes it straight
+// to counters[0] (pinned host memory in the solver loop, where it replaces a
+// 2-4 us copy per step).
+__device__ __forceinline__ void givens_arrive(int act, unsigned long long* arrive, int* counters) {
+  const unsigned long long old = atomicAdd(arrive, (1ULL << 32) | (unsigned)act);
+  if ((unsigned)(old >> 32) == gridDim.x - 1) {
+    *arrive = 0;  // for the next launch
+    __hip_atomic_store(counters, (int)(unsigned)old + act, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 template <typename T, int JM>
 __global__ void __launch_bounds__(KT) k_givens(int j, int B, int rows, const double* __restrict__ rowpart,
                                                int* __restrict__ active, c128* __restrict__ H,
                                                double* __restrict__ cs, c128* __restrict__ sn,
                                                c128* __restrict__ gv, const double* __restrict__ target,
                                                int* __restrict__ ncol, int* __restrict__ iters,
-                                               cplx<T>* __restrict__ vscale_next, int* __restrict__ counters) {
+                                               cplx<T>* __restrict__ vscale_next, int* __restrict__ counters,
+                                               unsigned long long* __restrict__ arrive) {
   __shared__ double red[KT / 64];
+  __shared__ c128 s_col[JM + 1], s_sn[JM];
+  __shared__ double s_cs[JM];
   const int b = blockIdx.x;
-  if (b >= B || !active[b]) return;  // uniform per workgroup
+  if (!active[b]) {  // uniform per workgroup
+    if (threadIdx.x == 0) givens_arrive(0, arrive, counters);
+    return;
+  }
+  c128* col = H + (long)b * (JM + 1) * JM + j;  // col[i*JM] = H[i][j]
+  if ((int)threadIdx.x <= j) s_col[threadIdx.x] = col[threadIdx.x * JM];
+  if ((int)threadIdx.x < j) {
+    s_cs[threadIdx.x] = cs[b * JM + threadIdx.x];
+    s_sn[threadIdx.x] = sn[b * JM + threadIdx.x];
+  }
   double s2 = 0.0;
   for (int k = threadIdx.x; k < rows; k += KT) s2 += rowpart[(long)b * rows + k];
-  s2 = block_sum<KT>(s2, red);
+  s2 = block_sum<KT>(s2, red);  // its barriers publish the column as well
   if (threadIdx.x != 0) return;
+  const c128 g = gv[b * (JM + 1) + j];
+  const double tg = target[b];
   const double hn = sqrt(s2);
-  c128* col = H + (long)b * (JM + 1) * JM + j;  // col[i*JM] = H[i][j]
+  c128 a = s_col[0];
   for (int i = 0; i < j; ++i) {
-    const c128 a = col[i * JM], c2 = col[(i + 1) * JM];
-    const double c = cs[b * JM + i];
-    const c128 s = sn[b * JM + i];
+    const c128 c2 = s_col[i + 1];
+    const double c = s_cs[i];
+    const c128 s = s_sn[i];
     col[i * JM] = c * a + s * c2;
-    col[(i + 1) * JM] = c * c2 - conj(s) * a;
+    a = c * c2 - conj(s) * a;
   }
-  const c128 a = col[j * JM];
   const double aa = sqrt(norm2(a));
   const double nu = sqrt(aa * aa + hn * hn);
   if (nu == 0.0) {
@@ -153,6 +179,7 @@ __global__ void __launch_bounds__(KT) k_givens(int j, int B, int rows, const dou
     // stops with the solution of the first j columns
     iters[b] += 1;
     active[b] = 0;
+    givens_arrive(0, arrive, counters);
     return;
   }
   double c;
@@ -168,19 +195,16 @@ __global__ void __launch_bounds__(KT) k_givens(int j, int B, int rows, const dou
   sn[b * JM + j] = s;
   col[j * JM] = c * a + hn * s;
   col[(j + 1) * JM] = mk(0.0, 0.0);
-  const c128 g = gv[b * (JM + 1) + j];
   gv[b * (JM + 1) + j] = c * g;
   const c128 g1 = (-1.0) * (conj(s) * g);
   gv[b * (JM + 1) + j + 1] = g1;
   ncol[b] = j + 1;
   iters[b] += 1;
   const double res = sqrt(norm2(g1));
-  if (res <= target[b] || !(hn > 1e-300) || nu == 0.0) {
-    active[b] = 0;
-  } else {
-    vscale_next[b] = mk((T)(1.0 / hn), (T)0);
-    atomicAdd(counters, 1);
-  }
+  const int act = !(res <= tg || !(hn > 1e-300));
+  if (act) vscale_next[b] = mk((T)(1.0 / hn), (T)0);
+  else active[b] = 0;
+  givens_arrive(act, arrive, counters);
 }
 
 // nrmp[b][blk] = sum of the block's share of the per-row partials of RHS b.
@@ -205,6 +229,7 @@ __global__ void __launch_bounds__(1024) k_cycle_init(int B, int nblk, int first,
                                                      double* __restrict__ rscale, int* __restrict__ active,
                                                      int* __restrict__ ncol, c128* __restrict__ gv,
                                                      int* __restrict__ counters, double* __restrict__ maxrel,
+                                                     unsigned long long* __restrict__ arrive,
                                                      cplx<T>* __restrict__ vscale0) {
   __shared__ double red[1024 / 64];
   __shared__ double redm[1024 / 64];
@@ -249,33 +274,40 @@ __global__ void __launch_bounds__(1024) k_cycle_init(int B, int nblk, int first,
     maxrel[0] = mm;
     counters[0] = (int)tot;
     counters[1] = (int)tot;
+    arrive[0] = 0;
   }
 }
 
-// Back-substitution R y = g for each RHS (k = ncol columns).
+// Back-substitution R y = g for each RHS (k = ncol columns), one wave per RHS:
+// the triangle is fetched at once into LDS, then column by column lane r
+// subtracts R[r][i] y_i (one thread per RHS reading the triangle from memory
+// entry by entry took 18 us at 14 columns and 57 at 20).
 template <typename T, int JM>
-__global__ void k_backsolve(int B, const int* __restrict__ ncol, const c128* __restrict__ H,
-                            const c128* __restrict__ gv, c128* __restrict__ y, const double* __restrict__ rnorm,
-                            const cplx<T>* __restrict__ vscale) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
+__global__ void __launch_bounds__(64) k_backsolve(int B, const int* __restrict__ ncol, const c128* __restrict__ H,
+                                                  const c128* __restrict__ gv, c128* __restrict__ y,
+                                                  const double* __restrict__ rnorm,
+                                                  const cplx<T>* __restrict__ vscale) {
+  __shared__ c128 R[JM][JM + 1];
+  const int b = blockIdx.x, lane = threadIdx.x;
   const int k = ncol[b];
   const c128* Hb = H + (long)b * (JM + 1) * JM;
-  for (int i = k - 1; i >= 0; --i) {
-    c128 acc = gv[(long)b * (JM + 1) + i];
-    for (int l = i + 1; l < k; ++l) acc = acc - Hb[i * JM + l] * y[(long)b * JM + l];
-    const c128 d = Hb[i * JM + i];
-    const double dn = norm2(d);
-    // acc / d (a zero diagonal cannot occur for a kept column; guarded anyway)
-    y[(long)b * JM + i] = dn > 0.0 ? mk((acc.x * d.x + acc.y * d.y) / dn, (acc.y * d.x - acc.x * d.y) / dn)
-                                   : mk(0.0, 0.0);
-  }
+  for (int e = lane; e < k * JM; e += 64) R[e / JM][e % JM] = Hb[e];
   // the basis is normalised by |r| (cycle start) and stored with scales
-  for (int i = 0; i < k; ++i) {
-    const double sc = rnorm[b] * (double)vscale[(long)i * B + b].x;
-    const c128 v = y[(long)b * JM + i];
-    y[(long)b * JM + i] = mk(sc * v.x, sc * v.y);
+  const double sc = lane < k ? rnorm[b] * (double)vscale[(long)lane * B + b].x : 0.0;
+  c128 acc = lane < k ? gv[(long)b * (JM + 1) + lane] : mk(0.0, 0.0);
+  c128 mine = mk(0.0, 0.0);
+  __syncthreads();
+  for (int i = k - 1; i >= 0; --i) {
+    // every lane forms y_i from lane i's right-hand side
+    const c128 a = mk(__shfl(acc.x, i, 64), __shfl(acc.y, i, 64));
+    const c128 d = R[i][i];
+    const double dn = norm2(d);
+    // a / d (a zero diagonal cannot occur for a kept column; guarded anyway)
+    const c128 yi = dn > 0.0 ? mk((a.x * d.x + a.y * d.y) / dn, (a.y * d.x - a.x * d.y) / dn) : mk(0.0, 0.0);
+    if (lane == i) mine = yi;
+    if (lane < i) acc = acc - R[lane][i] * yi;
   }
+  if (lane < k) y[(long)b * JM + lane] = mk(sc * mine.x, sc * mine.y);
 }
 
 // x_b += sum_{i < ncol_b} y_i V_i (FP64 accumulation, y from k_backsolve);
@@ -402,7 +434,7 @@ template <typename T>
 void krylov_cycle_init(const KrylovState<T>& s, int first, double rtol, double inner_rtol, hipStream_t st) {
   FWI_JM_SWITCH(s.JM, hipLaunchKernelGGL((k_cycle_init<T, JMC>), dim3(1), dim3(1024), 0, st, s.B, s.nblk, first, rtol,
                                           inner_rtol, s.nrmp, s.rnorm, s.bnorm, s.target, s.rscale, s.active, s.ncol,
-                                          s.gv, s.counters, s.maxrel, s.vscale));
+                                          s.gv, s.counters, s.maxrel, s.arrive, s.vscale));
   FWI_LAUNCH_CHECK();
 }
 
@@ -419,7 +451,7 @@ void krylov_dots(const KrylovState<T>& s, int j, hipStream_t st) {
 template <typename T>
 void krylov_hsum(const KrylovState<T>& s, int j, int ndot, hipStream_t st) {
   FWI_JM_SWITCH(s.JM, hipLaunchKernelGGL((k_hsum<T, JMC>), dim3(s.B), dim3(KT), 0, st, j, s.B, s.active, s.vscale,
-                                          s.dotp, ndot, s.H, s.hcoef, s.counters));
+                                          s.dotp, ndot, s.H, s.hcoef));
   FWI_LAUNCH_CHECK();
 }
 
@@ -427,13 +459,13 @@ template <typename T>
 void krylov_givens(const KrylovState<T>& s, int j, const double* rowpart, int rows, hipStream_t st) {
   FWI_JM_SWITCH(s.JM, hipLaunchKernelGGL((k_givens<T, JMC>), dim3(s.B), dim3(KT), 0, st,
                                           j, s.B, rows, rowpart, s.active, s.H, s.cs, s.sn, s.gv, s.target, s.ncol,
-                                          s.iters, s.vscale + (long)(j + 1) * s.B, s.counters));
+                                          s.iters, s.vscale + (long)(j + 1) * s.B, s.counters, s.arrive));
   FWI_LAUNCH_CHECK();
 }
 
 template <typename T>
 void krylov_backsolve(const KrylovState<T>& s, hipStream_t st) {
-  FWI_JM_SWITCH(s.JM, hipLaunchKernelGGL((k_backsolve<T, JMC>), dim3((s.B + 63) / 64), dim3(64), 0, st, s.B,
+  FWI_JM_SWITCH(s.JM, hipLaunchKernelGGL((k_backsolve<T, JMC>), dim3(s.B), dim3(64), 0, st, s.B,
                                           s.ncol, s.H, s.gv, s.y, s.rnorm, s.vscale));
   FWI_LAUNCH_CHECK();
 }

@@ -31,8 +31,9 @@ struct KrylovState {
   int* active = nullptr;       // [B]
   int* ncol = nullptr;         // [B]
   int* iters = nullptr;        // [B] accumulated iterations
-  int* counters = nullptr;     // [0] active count, [1] unconverged
-  double* maxrel = nullptr;    // [1] max relative residual at cycle start
+  int* counters = nullptr;     // [0] active count, [1] active at the cycle start; device or pinned host memory
+  double* maxrel = nullptr;    // [1] max relative residual at cycle start; likewise
+  unsigned long long* arrive = nullptr;  // k_givens: workgroups arrived (high word), active RHS among them (low)
   long vstride() const { return (long)B * n; }
 };
 
@@ -43,7 +44,9 @@ int krylov_nblk(long n);
 // grid row; fold those into nrmp.
 template <typename T>
 void krylov_rows_norm(const KrylovState<T>& s, const double* rowpart, int rows, hipStream_t st);
-// Norms, activity, stopping targets and the scale of V_0 (1 / |r|).
+// Norms, activity, stopping targets and the scale of V_0 (1 / |r|); counters
+// and maxrel are written once, by one thread, so they may be host memory that
+// the host reads after the kernel's event.
 template <typename T>
 void krylov_cycle_init(const KrylovState<T>& s, int first, double rtol, double inner_rtol, hipStream_t st);
 // Arnoldi step j after the matvec w = A v_j stored into V_{j+1}:
@@ -57,7 +60,7 @@ template <typename T>
 void krylov_hsum(const KrylovState<T>& s, int j, int ndot, hipStream_t st);
 // after that pass: the norm of the orthogonalised vector from its per-row
 // sums (rows per RHS), Givens rotations, convergence, scale of V_{j+1} and
-// the active count.
+// the active count (counters[0], written once, as in krylov_cycle_init).
 template <typename T>
 void krylov_givens(const KrylovState<T>& s, int j, const double* rowpart, int rows, hipStream_t st);
 // Back-substitution: y from the rotated Hessenberg system, scaled so that
