@@ -840,7 +840,7 @@ constexpr int kGradSeg = 16;
 // a serial chain of k steps, about 1.7 us each (a workgroup's 64 x 64 x 16
 // products at one compute unit's share of the FP64 matrix rate, or the load
 // latency where only a few 16-blocks are used), so small grids are cut to 64
-// points per split up to 128 splits (64^2 with 16 elements: 4 splits of 1024
+// points per split up to 96 splits (64^2 with 16 elements: 4 splits of 1024
 // took 160 us). From 131072 points on, one split per 1024 points: 64 while
 // the output tiles and frequencies already give >= 1024 workgroups, more (up
 // to 512) when they do not (a 3D grid with one frequency and 64 x 64 outputs
@@ -848,7 +848,7 @@ constexpr int kGradSeg = 16;
 // chunk sums its data in the same order as the whole frequency.
 // gemm_splits_max bounds every launch's count (buffer plans).
 int gemm_splits_max(long n) {
-  const long s = std::min<long>(std::max<long>(128, (n + 1023) / 1024), (n + 63) / 64);
+  const long s = std::min<long>(std::max<long>(96, (n + 1023) / 1024), (n + 63) / 64);
   return (int)(s < 1 ? 1 : (s > 512 ? 512 : s));
 }
 int gemm_splits(long n, int nf, int ni, int nj) {

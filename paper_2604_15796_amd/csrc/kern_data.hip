@@ -9,6 +9,7 @@
 //  * TV operators, shrinkage and dual update (Eq. 13-14), CG vector updates.
 // All accumulations are FP64 with fixed-order two-stage reductions.
 #include <algorithm>
+#include <type_traits>
 
 #include "data.hpp"
 
@@ -44,15 +45,24 @@ constexpr int GK = 16;  // k step
 // multiplied. Compile-time: with run-time bounds the loads end up behind
 // branches and are waited for one by one (1450 against 740 us for J a and
 // J^H b at 256^2, 8 frequencies, 64 elements).
+// Three workgroups per compute unit (the launch bound keeps the registers to
+// 168): a last one left alone on its compute unit runs at half its rate.
+// upper: blockIdx.y counts the tile pairs ti < tj of a symmetric product.
 template <int NB>
-__global__ void __launch_bounds__(256) k_gemm_nt(const c128* __restrict__ A, long a_ls, int ni,
+__global__ void __launch_bounds__(256, 3) k_gemm_nt(const c128* __restrict__ A, long a_ls, int ni,
                                                  const c128* __restrict__ w, const c128* __restrict__ Bm, long b_ls,
-                                                 int nj, long n, long kchunk, c128* __restrict__ part, int nf) {
+                                                 int nj, long n, long kchunk, c128* __restrict__ part, int nf,
+                                                 int upper) {
   __shared__ c128 sa[GT][GK + 1];
   __shared__ c128 sb[GT][GK + 1];
   const int ks = blockIdx.x;
   const int tj_n = (nj + GT - 1) / GT;
-  const int ti = blockIdx.y / tj_n, tj = blockIdx.y % tj_n;
+  int ti = blockIdx.y / tj_n, tj = blockIdx.y % tj_n;
+  if (upper) {
+    tj = blockIdx.y;
+    for (ti = 0; tj >= tj_n - 1 - ti; ++ti) tj -= tj_n - 1 - ti;
+    tj += ti + 1;
+  }
   const int l = blockIdx.z;
   const int t = threadIdx.x;
   const int lane = t & 63, wv = t >> 6;
@@ -116,27 +126,149 @@ __global__ void __launch_bounds__(256) k_gemm_nt(const c128* __restrict__ A, lon
     }
 }
 
+// Symmetric product C[l][i][j] = coef_l sum_n F[l][i][n] w[n] F[l][j][n] (the
+// Jacobian product of element transmits: both operands are the same fields).
+// Tile pairs ti < tj go to k_gemm_nt; this kernel does the diagonal tiles, the
+// 16 x 16 blocks of each unordered pair once: wave w takes block pairs {w, w}
+// and {w, w + 1} (mod 4) for every k step and half of the k steps of pair
+// {w mod 2, w mod 2 + 2}: 2.5 of the 4 block products per wave of the general
+// tile, the same for all waves, and each field element is fetched once. Bound
+// by the FP64 matrix cores, as the general product is: 209 us at 256^2, 8
+// frequencies, 64 elements, against 327 (both kinds of tile in one kernel need
+// 266 registers, one workgroup per compute unit: 300 us).
+template <int NB>
+__global__ void __launch_bounds__(256, 3) k_gemm_sym(const c128* __restrict__ F, long f_ls, int ni,
+                                                     const c128* __restrict__ w, long n, long kchunk,
+                                                     c128* __restrict__ part, int nf) {
+  __shared__ c128 sa[GT][GK + 1];
+  __shared__ c128 sb[GT][GK + 1];
+  const int ks = blockIdx.x, ti = blockIdx.y, l = blockIdx.z;
+  const int t = threadIdx.x;
+  const int lane = t & 63, wv = t >> 6;
+  const c128* Fl = F + l * f_ls;
+  constexpr int NA = 3;  // blocks (wv, wv), (wv, wv + 1), (wv mod 2, wv mod 2 + 2)
+  v4d cr[NA], ci[NA];
+#pragma unroll
+  for (int b = 0; b < NA; ++b) {
+    cr[b] = v4d{0.0, 0.0, 0.0, 0.0};
+    ci[b] = v4d{0.0, 0.0, 0.0, 0.0};
+  }
+  const long k0 = ks * kchunk;
+  const long k1 = min(n, k0 + kchunk);
+  const int r0 = t / GK, kc0 = t % GK;
+  c128 ra[NB], rw;
+  auto fetch = [&](long kb) {
+    const long kc = kb + kc0 < k1 ? kb + kc0 : k1 - 1;
+    rw = w[kc];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int ia = ti * GT + r0 + 16 * q;
+      ra[q] = Fl[(long)(ia < ni ? ia : ni - 1) * n + kc];
+    }
+  };
+  const int li = lane & 15, lk = lane >> 4;
+  const int col1 = (wv + 1) & 3, row2 = wv & 1, col2 = row2 + 2, c2 = (wv >> 1) * (GK / 2);
+  if (k0 < k1) fetch(k0);
+  for (long kb = k0; kb < k1; kb += GK) {
+    const bool vk = kb + kc0 < k1;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const bool ok = vk && ti * GT + r0 + 16 * q < ni;
+      sa[r0 + 16 * q][kc0] = ok ? ra[q] * rw : mk(0.0, 0.0);
+      sb[r0 + 16 * q][kc0] = ok ? ra[q] : mk(0.0, 0.0);
+    }
+    __syncthreads();
+    if (kb + GK < k1) fetch(kb + GK);
+    if (NB == 4 || wv < NB) {
+#pragma unroll
+      for (int c = 0; c < GK; c += 4) {
+        const c128 av = sa[16 * wv + li][c + lk];
+        cmfma(av, sb[16 * wv + li][c + lk], cr[0], ci[0]);
+        if (NB == 4 || col1 < NB) cmfma(av, sb[16 * col1 + li][c + lk], cr[1], ci[1]);
+      }
+    }
+    if (NB == 4 || col2 < NB) {
+#pragma unroll
+      for (int c = 0; c < GK / 2; c += 4)
+        cmfma(sa[16 * row2 + li][c2 + c + lk], sb[16 * col2 + li][c2 + c + lk], cr[2], ci[2]);
+    }
+    __syncthreads();
+  }
+  // block (row, col) of the tile to its place; the second half of pair
+  // {0, 2} / {1, 3} to the mirrored place, which no block covers otherwise
+  auto put = [&](int row, int col, bool mirror, const v4d& xr, const v4d& xi) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = ti * GT + 16 * row + (lane >> 4) + 4 * v, j = ti * GT + 16 * col + (lane & 15);
+      if (i < ni && j < ni)
+        part[(((long)ks * nf + l) * ni + (mirror ? j : i)) * ni + (mirror ? i : j)] = mk(xr[v], xi[v]);
+    }
+  };
+  put(wv, wv, false, cr[0], ci[0]);
+  put(wv, col1, false, cr[1], ci[1]);
+  put(row2, col2, wv >= 2, cr[2], ci[2]);
+}
+
+// Where element (i, j) of the symmetric product lies in the partials: its own
+// place, the mirrored one, or both (halves of the k steps).
+__device__ __forceinline__ void sym_place(int i, int j, bool& own, bool& mirror) {
+  const int ti = i / GT, tj = j / GT;
+  if (ti != tj) {
+    own = ti < tj;
+    mirror = !own;
+    return;
+  }
+  const int d = ((j % GT) / 16 - (i % GT) / 16) & 3;
+  own = d != 3;
+  mirror = d >= 2;
+}
+
 // Sum of the split-K partials part[nks][tot] in a fixed order: a workgroup
 // takes 64 consecutive outputs, wave w sums the splits w, w + 16, ... (one
 // coalesced row of 64 per split), then the 16 wave sums are added in wave
 // order.
+// SYM: the partials of the symmetric product (see sym_place); the sums of the
+// places that hold some, unscaled (k_sym_fill completes them).
+template <bool SYM>
 __global__ void __launch_bounds__(1024) k_gemm_nt_final(const c128* __restrict__ part, int nks, int nf, int ni,
                                                         int nj, const c128* __restrict__ coef, c128* __restrict__ C) {
   __shared__ c128 red[16][64];
   const long tot = (long)nf * ni * nj;
   const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6;
   const long idx = (long)blockIdx.x * 64 + lane;
+  bool own = idx < tot;
+  if constexpr (SYM) {
+    bool mirror;
+    if (own) sym_place((int)(idx / nj % ni), (int)(idx % nj), own, mirror);
+  }
   c128 s = mk(0.0, 0.0);
-  if (idx < tot)
+  if (own)
     for (int k = w; k < nks; k += 16) s = s + part[(long)k * tot + idx];
   red[w][lane] = s;
   __syncthreads();
-  if (w == 0 && idx < tot) {
+  if (w == 0 && own) {
     c128 t = red[0][lane];
 #pragma unroll
     for (int q = 1; q < 16; ++q) t = t + red[q][lane];
-    C[idx] = coef[(int)(idx / ((long)ni * nj))] * t;
+    C[idx] = SYM ? t : coef[(int)(idx / ((long)ni * nj))] * t;
   }
+}
+
+// C[l][i][j] = C[l][j][i] = coef_l times the sum of the places that hold a part
+// of the pair; one thread per pair i <= j, in place.
+__global__ void __launch_bounds__(256) k_sym_fill(int nf, int ni, const c128* __restrict__ coef, c128* C) {
+  const long tot = (long)nf * ni * ni, idx = (long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= tot) return;
+  const int l = (int)(idx / ((long)ni * ni)), i = (int)(idx / ni % ni), j = (int)(idx % ni);
+  if (i > j) return;
+  const long mir = ((long)l * ni + j) * ni + i;
+  bool own, mirror;
+  sym_place(i, j, own, mirror);
+  c128 v = own ? C[idx] : mk(0.0, 0.0);
+  if (mirror && i != j) v = v + C[mir];
+  v = coef[l] * v;
+  C[idx] = v;
+  C[mir] = v;
 }
 
 // ------------------------------------------------------------- gemm (NN) ---
@@ -253,6 +385,105 @@ __global__ void __launch_bounds__(256) k_gemm_cn(const c128* __restrict__ M, int
       part[((long)l * gridDim.y + blockIdx.y) * n + n0 + t] = s;
     }
   }
+}
+
+// J^H b of element transmits (transmit and receiver fields are one array P):
+// sum_ij conj(M_ij) P_i[n] P_j[n] is a quadratic form, so every unordered pair
+// of 16-blocks of elements is multiplied once, with conj(M_ij + M_ji) for i, j
+// in different blocks. Row tiles of 64: column tiles before the row tile are
+// skipped; in the diagonal tile column block c meets row blocks c, c - 1
+// (mod 4) and, for c >= 2, c - 2 (10 of the 16 block products). A wave owns 16
+// grid points and every row block, so the pairs are compile-time and equal
+// for all waves, and the sum over the rows stays inside the wave. Bound by the
+// FP64 matrix cores: 285 us at 256^2, 8 frequencies, 64 elements, against 431
+// for k_gemm_cn<true>; 0.66 against 1.09 ms per 3 frequencies of 384^2 with
+// 128 elements. part [nf][row tiles][n] as in k_gemm_cn<true>.
+template <int NB>
+__global__ void __launch_bounds__(256) k_gemm_cn_sym(const c128* __restrict__ M, int ni, const c128* __restrict__ P,
+                                                     long p_ls, long n, const c128* __restrict__ k2,
+                                                     c128* __restrict__ part) {
+  __shared__ c128 sm[CT][CK + 1];   // conj(M_ij [+ M_ji]) tile [i][j]
+  __shared__ c128 sp[CK][CT + 1];   // P tile [j][n]
+  const int l = blockIdx.z;
+  const int i0 = blockIdx.y * CT;
+  const long n0 = (long)blockIdx.x * CT;
+  const int t = threadIdx.x;
+  const int lane = t & 63, wv = t >> 6, li = lane & 15, lk = lane >> 4;
+  const c128* Ml = M + (long)l * ni * ni;
+  const c128* Pl = P + l * p_ls;
+  v4d cr[NB], ci[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    cr[b] = v4d{0.0, 0.0, 0.0, 0.0};
+    ci[b] = v4d{0.0, 0.0, 0.0, 0.0};
+  }
+  const int mr = t / CK, mc = t % CK, pr = t / CT, pc = t % CT;  // first element of the thread in each tile
+  constexpr int Q = CT * CK / 256;
+  c128 rm[NB], rt[NB], rp[Q];
+  auto fetch = [&](int jb) {
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int i = i0 + mr + 16 * q, j = jb + mc;
+      const int ic = i < ni ? i : ni - 1, jc = j < ni ? j : ni - 1;
+      rm[q] = Ml[(long)ic * ni + jc];
+      rt[q] = Ml[(long)jc * ni + ic];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int j = jb + pr + 4 * q;
+      const long nn = n0 + pc;
+      rp[q] = Pl[(long)(j < ni ? j : ni - 1) * n + (nn < n ? nn : n - 1)];
+    }
+  };
+  // D: the tile's distance from the diagonal tile's column block CB (compile time)
+  auto step = [&](int jb, auto cb_tag, bool last) {
+    constexpr int CB = decltype(cb_tag)::value;  // column block of the diagonal tile, or -1 past it
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const bool ok = i0 + mr + 16 * q < ni && jb + mc < ni;
+      const c128 v = q == CB ? rm[q] : rm[q] + rt[q];
+      sm[mr + 16 * q][mc] = ok ? conj(v) : mk(0.0, 0.0);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      sp[pr + 4 * q][pc] = jb + pr + 4 * q < ni && n0 + pc < n ? rp[q] : mk(0.0, 0.0);
+    __syncthreads();
+    if (!last) fetch(jb + CK);
+#pragma unroll
+    for (int c = 0; c < CK; c += 4) {
+      // A[i][k] = sm[16 r + i][c + k], B[k][j] = sp[c + k][16 wv + j]
+      const c128 pv = sp[c + lk][16 * wv + li];
+#pragma unroll
+      for (int r = 0; r < NB; ++r) {
+        const bool use = CB < 0 || r == CB || r == ((CB + 3) & 3) || (CB >= 2 && r == CB - 2);
+        if (use) cmfma(sm[16 * r + li][c + lk], pv, cr[r], ci[r]);
+      }
+    }
+    __syncthreads();
+  };
+  fetch(i0);
+  step(i0, std::integral_constant<int, 0>{}, i0 + CK >= ni);
+  if (NB > 1 && i0 + CK < ni) step(i0 + CK, std::integral_constant<int, 1>{}, i0 + 2 * CK >= ni);
+  if (NB > 2 && i0 + 2 * CK < ni) step(i0 + 2 * CK, std::integral_constant<int, 2>{}, i0 + 3 * CK >= ni);
+  if (NB > 3 && i0 + 3 * CK < ni) step(i0 + 3 * CK, std::integral_constant<int, 3>{}, i0 + 4 * CK >= ni);
+  if constexpr (NB == 4)
+    for (int jb = i0 + CT; jb < ni; jb += CK) step(jb, std::integral_constant<int, -1>{}, jb + CK >= ni);
+  const c128 kc = conj(k2[l]);
+  const long nn = n0 + 16 * wv + li;
+  c128 acc = mk(0.0, 0.0);
+#pragma unroll
+  for (int r = 0; r < NB; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = i0 + 16 * r + lk + 4 * v;
+      if (i < ni && nn < n) acc = acc + kc * conj(Pl[(long)i * n + nn] * mk(cr[r][v], ci[r][v]));
+    }
+  double ax = acc.x, ay = acc.y;
+  ax += __shfl_xor(ax, 16, 64);
+  ay += __shfl_xor(ay, 16, 64);
+  ax += __shfl_xor(ax, 32, 64);
+  ay += __shfl_xor(ay, 32, 64);
+  if (lane < 16 && nn < n) part[((long)l * gridDim.y + blockIdx.y) * n + nn] = mk(ax, ay);
 }
 
 // ------------------------------------------------------------- residual ---
@@ -470,35 +701,72 @@ __global__ void k_copy_scalar(const double* __restrict__ in, double* __restrict_
 void launch_gemm_nt(int nf, const c128* A, long a_ls, int ni, const c128* w, const c128* Bm, long b_ls, int nj, long n,
                     const c128* coef, c128* part, int nks, c128* C, hipStream_t st) {
   long kchunk = (n + nks - 1) / nks;
-  kchunk = (kchunk + GK - 1) / GK * GK;
+  // whole k steps (256 bytes of each row), and an odd number of them, so that
+  // the splits start on different memory channels also where rows and splits
+  // are powers of two
+  kchunk = ((kchunk + GK - 1) / GK | 1) * GK;
   const int tiles = ((ni + GT - 1) / GT) * ((nj + GT - 1) / GT);
   const int nb = (std::max(ni, nj) + 15) / 16;
+  const long tot = (long)nf * ni * nj;
+  const dim3 fin((unsigned)((tot + 63) / 64));
+  if (A == Bm && a_ls == b_ls && ni == nj && w) {
+    // one array on both sides: the product is symmetric in (i, j)
+    const int T = (ni + GT - 1) / GT;
+    const dim3 diag(nks, T, nf);
+#define FWI_GEMM_SYM(NB) \
+  hipLaunchKernelGGL(k_gemm_sym<NB>, diag, dim3(256), 0, st, A, a_ls, ni, w, n, kchunk, part, nf)
+    if (nb == 1) FWI_GEMM_SYM(1);
+    else if (nb == 2) FWI_GEMM_SYM(2);
+    else if (nb == 3) FWI_GEMM_SYM(3);
+    else FWI_GEMM_SYM(4);
+#undef FWI_GEMM_SYM
+    FWI_LAUNCH_CHECK();
+    if (T > 1) {
+      hipLaunchKernelGGL(k_gemm_nt<4>, dim3(nks, T * (T - 1) / 2, nf), dim3(256), 0, st, A, a_ls, ni, w, Bm, b_ls, nj,
+                         n, kchunk, part, nf, 1);
+      FWI_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(k_gemm_nt_final<true>, fin, dim3(1024), 0, st, part, nks, nf, ni, nj, coef, C);
+    FWI_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_sym_fill, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, nf, ni, coef, C);
+    FWI_LAUNCH_CHECK();
+    return;
+  }
   const dim3 grid(nks, tiles, nf);
 #define FWI_GEMM_NT(NB) \
-  hipLaunchKernelGGL(k_gemm_nt<NB>, grid, dim3(256), 0, st, A, a_ls, ni, w, Bm, b_ls, nj, n, kchunk, part, nf)
+  hipLaunchKernelGGL(k_gemm_nt<NB>, grid, dim3(256), 0, st, A, a_ls, ni, w, Bm, b_ls, nj, n, kchunk, part, nf, 0)
   if (nb == 1) FWI_GEMM_NT(1);
   else if (nb == 2) FWI_GEMM_NT(2);
   else if (nb == 3) FWI_GEMM_NT(3);
   else FWI_GEMM_NT(4);
 #undef FWI_GEMM_NT
   FWI_LAUNCH_CHECK();
-  const long tot = (long)nf * ni * nj;
-  hipLaunchKernelGGL(k_gemm_nt_final, dim3((unsigned)((tot + 63) / 64)), dim3(1024), 0, st, part, nks, nf, ni, nj,
-                     coef, C);
+  hipLaunchKernelGGL(k_gemm_nt_final<false>, fin, dim3(1024), 0, st, part, nks, nf, ni, nj, coef, C);
   FWI_LAUNCH_CHECK();
 }
 
 void launch_gemm_cn(int nf, const c128* M, int ni, int nj, const c128* P, long p_ls, long n, c128* S, long s_ls,
                     hipStream_t st) {
-  hipLaunchKernelGGL(k_gemm_cn<false>, dim3((unsigned)((n + CT - 1) / CT), (ni + CT - 1) / CT, nf), dim3(256), 0, st,
+  hipLaunchKernelGGL((k_gemm_cn<false>), dim3((unsigned)((n + CT - 1) / CT), (ni + CT - 1) / CT, nf), dim3(256), 0, st,
                      M, ni, nj, P, p_ls, n, S, s_ls, nullptr, 0L, nullptr, nullptr);
   FWI_LAUNCH_CHECK();
 }
 int gemm_cn_grad_segments(int nf, int ni) { return nf * ((ni + CT - 1) / CT); }
 void launch_gemm_cn_grad(int nf, const c128* M, int ni, int nj, const c128* P, long p_ls, long n, const c128* T,
                          long t_ls, const c128* k2, c128* part, hipStream_t st) {
-  hipLaunchKernelGGL(k_gemm_cn<true>, dim3((unsigned)((n + CT - 1) / CT), (ni + CT - 1) / CT, nf), dim3(256), 0, st,
-                     M, ni, nj, P, p_ls, n, nullptr, 0L, T, t_ls, k2, part);
+  const dim3 grid((unsigned)((n + CT - 1) / CT), (ni + CT - 1) / CT, nf);
+  if (T == P && t_ls == p_ls && ni == nj)  // one array on both sides: a quadratic form
+  {
+    const int nb = (ni + 15) / 16;
+#define FWI_GEMM_CNS(NB) hipLaunchKernelGGL(k_gemm_cn_sym<NB>, grid, dim3(256), 0, st, M, ni, P, p_ls, n, k2, part)
+    if (nb == 1) FWI_GEMM_CNS(1);
+    else if (nb == 2) FWI_GEMM_CNS(2);
+    else if (nb == 3) FWI_GEMM_CNS(3);
+    else FWI_GEMM_CNS(4);
+#undef FWI_GEMM_CNS
+  } else {
+    hipLaunchKernelGGL((k_gemm_cn<true>), grid, dim3(256), 0, st, M, ni, nj, P, p_ls, n, nullptr, 0L, T, t_ls, k2, part);
+  }
   FWI_LAUNCH_CHECK();
 }
 void launch_grad_sum(long n, const c128* part, int nseg, int first, c128* acc, hipStream_t st) {

@@ -38,3 +38,17 @@ def test_jacobian_products_at_tile_edges_vs_oracle(ctx, nx, nz, ne, nt):
     a = W.random_complex(3, (p.n,))
     ref = O.jacobian_apply_tx(tx, rx, a, p.freqs, p.c0, p.dx, 2)
     assert _err(ctx.jacobian_apply_tx(p, _dev(tx), _dev(rx), _dev(a)).cpu().numpy(), ref) < 1e-12
+
+
+@pytest.mark.parametrize("nx,nz,ne", [(5, 3, 1), (9, 7, 15), (64, 1, 16), (13, 10, 17), (41, 5, 33), (16, 16, 48),
+                                      (31, 9, 49), (4099 // 11, 11, 64), (64, 64, 65), (30, 20, 130)])
+def test_symmetric_jacobian_products_at_tile_edges_vs_oracle(ctx, nx, nz, ne):
+    """Element transmits: transmit and receiver fields are one array, so the
+    products run on the unordered pairs of element blocks."""
+    p = W.small2d(seed=nx + ne, nx=nx, nz=nz, ne=ne, nf=2)
+    f, a, b = W.random_complex(1, (p.nf, ne, p.n)), W.random_complex(3, (p.n,)), W.random_complex(4, (p.nf, ne, ne))
+    ref = O.jacobian_apply(f, a, p.freqs, p.c0, p.dx, 2)
+    assert _err(ctx.jacobian_apply(p, _dev(f), _dev(a)).cpu().numpy(), ref) < 1e-12
+    k2 = np.array([O.wavenumber(q, p.c0) ** 2 for q in p.freqs])
+    ref = p.dx ** 2 * sum(k2[l] * np.conj(np.sum(f[l] * (np.conj(b[l]) @ f[l]), axis=0)) for l in range(p.nf))
+    assert _err(ctx.jacobian_adjoint_apply(p, _dev(f), _dev(b)).cpu().numpy(), ref) < 1e-12
