@@ -127,12 +127,12 @@ __device__ __forceinline__ c128 expikr(c128 k, double r) {
 // linear convolution of an n-point axis).
 __global__ void k_green_table(int dim, int nx, int ny, int nz, int Lx, int Ly, int Lz, double dx, c128 k,
                               c128 fac, c128 self, double scale, c128* __restrict__ T) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long total = (long)Lx * Ly * Lz;
+  // at most 1024 points per axis: 32-bit index arithmetic
+  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned total = (unsigned)Lx * Ly * Lz;
   if (i >= total) return;
-  const int ix = (int)(i % Lx);
-  const int iy = (int)((i / Lx) % Ly);
-  const int iz = (int)(i / ((long)Lx * Ly));
+  const unsigned row = i / (unsigned)Lx;
+  const int ix = (int)(i - row * Lx), iy = (int)(row % (unsigned)Ly), iz = (int)(row / (unsigned)Ly);
   auto off = [](int idx, int n, int L, bool& ok) -> int {
     if (idx < n) return idx;
     if (idx > L - n) return idx - L;
@@ -149,8 +149,8 @@ __global__ void k_green_table(int dim, int nx, int ny, int nz, int Lx, int Ly, i
     if (r == 0.0) {
       v = self;
     } else if (dim == 2 && k.y == 0.0) {
-      double j0, j1, y0, y1;
-      bessel01(k.x * r, &j0, &j1, &y0, &y1);
+      double j0, y0;
+      hankel0(k.x * r, &j0, &y0);
       // (i/4) H0 = (i/4)(J0 + i Y0) = (-Y0/4, J0/4)
       v = mk(-0.25 * fac.x * y0, 0.25 * fac.x * j0);
     } else if (dim == 2) {
@@ -172,43 +172,66 @@ void launch_green_table(const Geo& g, c128 k, c128* table, hipStream_t st) {
   FWI_LAUNCH_CHECK();
 }
 
-// P0[e][n] = G(k |x_n - x_e|): 2D (i/4) H0^(1), 3D e^{ikr}/(4 pi r); with an
-// aperture, the average of G over the element's rectangle on the top face
-// (product Gauss-Legendre rule: sub-point x_e + (hw xi_a, hh xi_b, 0) with
-// weight w_a w_b / 4, one point in a direction of zero extent).
-__global__ void k_incident(int dim, int nx, int ny, int nz, double dx, c128 k, int ne,
-                           const double* __restrict__ exyz, Aperture ap, c128* __restrict__ P0) {
-  const long n = (long)nx * ny * nz;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+// G(k r): 2D (i/4) H0^(1)(k r), 3D e^{ikr}/(4 pi r).
+__device__ __forceinline__ c128 green_of(int dim, c128 k, double r) {
+  if (dim == 2 && k.y == 0.0) {
+    double j0, y0;
+    hankel0(k.x * r, &j0, &y0);
+    return mk(-0.25 * y0, 0.25 * j0);
+  }
+  if (dim == 2) {
+    const cz h = chankel0(cz{k.x * r, k.y * r});
+    return mk(-0.25 * h.im, 0.25 * h.re);
+  }
+  return (1.0 / (4.0 * PI * r)) * expikr(k, r);
+}
+
+// Distance of cell (ix, iy, iz)'s centre from a point, every operation rounded
+// by itself: the phase k r then has the rounding of plain FP64 coordinates.
+__device__ __forceinline__ double cell_distance(int dim, int ix, int iy, int iz, double dx, double ex, double ey,
+                                                double ez) {
+#pragma clang fp contract(off)
+  const double px = (ix + 0.5) * dx - ex, py = (dim == 3 ? (iy + 0.5) * dx : 0.0) - ey, pz = (iz + 0.5) * dx - ez;
+  return sqrt(px * px + py * py + pz * pz);
+}
+
+// As a call: inlined into a loop, the polynomial coefficients of the Hankel
+// function are kept in registers across its iterations and spill.
+__device__ __attribute__((noinline)) c128 green_call(int dim, c128 k, double r) { return green_of(dim, k, r); }
+
+// P0[e][n] = G(k |x_n - x_e|); with an aperture (APERTURE), the average of G
+// over the element's rectangle on the top face (product Gauss-Legendre rule:
+// sub-point x_e + (hw xi_a, hh xi_b, 0) with weight w_a w_b / 4, one point in a
+// direction of zero extent). Point elements have a kernel without the loops
+// and the call.
+template <bool APERTURE>
+__global__ void __launch_bounds__(256) k_incident(int dim, unsigned nx, unsigned ny, unsigned nz, double dx, c128 k,
+                                                  int ne, const double* __restrict__ exyz, Aperture ap,
+                                                  c128* __restrict__ P0) {
+  // at most 512 cells per axis: 32-bit index arithmetic
+  const unsigned n = nx * ny * nz;
+  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
   const int e = blockIdx.y;
   if (i >= n) return;
-  const int ix = (int)(i % nx);
-  const int iy = (int)((i / nx) % ny);
-  const int iz = (int)(i / ((long)nx * ny));
-  const int qa = ap.hw > 0.0 ? ap.rule.q : 1, qb = ap.hh > 0.0 ? ap.rule.q : 1;
-  c128 v = mk(0.0, 0.0);
-  for (int a = 0; a < qa; ++a) {
-    const double sx = ap.hw > 0.0 ? ap.hw * ap.rule.x[a] : 0.0;
-    const double wa = ap.hw > 0.0 ? 0.5 * ap.rule.w[a] : 1.0;
-    for (int b = 0; b < qb; ++b) {
-      const double sy = ap.hh > 0.0 ? ap.hh * ap.rule.x[b] : 0.0;
-      const double wb = ap.hh > 0.0 ? 0.5 * ap.rule.w[b] : 1.0;
-      const double px = (ix + 0.5) * dx - (exyz[3 * e + 0] + sx);
-      const double py = (dim == 3 ? (iy + 0.5) * dx : 0.0) - (exyz[3 * e + 1] + sy);
-      const double pz = (iz + 0.5) * dx - exyz[3 * e + 2];
-      const double r = sqrt(px * px + py * py + pz * pz);
-      c128 gv;
-      if (dim == 2 && k.y == 0.0) {
-        double j0, j1, y0, y1;
-        bessel01(k.x * r, &j0, &j1, &y0, &y1);
-        gv = mk(-0.25 * y0, 0.25 * j0);
-      } else if (dim == 2) {
-        const cz h = chankel0(cz{k.x * r, k.y * r});
-        gv = mk(-0.25 * h.im, 0.25 * h.re);
-      } else {
-        gv = (1.0 / (4.0 * PI * r)) * expikr(k, r);
+  const unsigned row = i / nx;
+  const int ix = (int)(i - row * nx), iy = (int)(row % ny), iz = (int)(row / ny);
+  const double ex = exyz[3 * e], ey = exyz[3 * e + 1], ez = exyz[3 * e + 2];
+  c128 v;
+  if constexpr (!APERTURE) {
+    v = green_of(dim, k, cell_distance(dim, ix, iy, iz, dx, ex, ey, ez));
+  } else {
+    const int qa = ap.hw > 0.0 ? ap.rule.q : 1, qb = ap.hh > 0.0 ? ap.rule.q : 1;
+    v = mk(0.0, 0.0);
+#pragma unroll 1
+    for (int a = 0; a < qa; ++a) {
+      const double sx = ap.hw > 0.0 ? ap.hw * ap.rule.x[a] : 0.0;
+      const double wa = ap.hw > 0.0 ? 0.5 * ap.rule.w[a] : 1.0;
+#pragma unroll 1
+      for (int b = 0; b < qb; ++b) {
+        const double sy = ap.hh > 0.0 ? ap.hh * ap.rule.x[b] : 0.0;
+        const double wb = ap.hh > 0.0 ? 0.5 * ap.rule.w[b] : 1.0;
+        v = v + (wa * wb) * green_call(dim, k, cell_distance(dim, ix, iy, iz, dx, ex + sx, ey + sy, ez));
       }
-      v = v + (wa * wb) * gv;
     }
   }
   P0[(long)e * n + i] = v;
@@ -218,8 +241,11 @@ void launch_incident(const Geo& g, c128 k, int ne, const double* exyz, const Ape
                      hipStream_t st) {
   const long n = g.n();
   if (n == 0 || ne == 0) return;
-  hipLaunchKernelGGL(k_incident, dim3((unsigned)((n + 255) / 256), ne), dim3(256), 0, st, g.dim, g.nx, g.ny, g.nz, g.dx,
-                     k, ne, exyz, ap, P0);
+  const dim3 grid((unsigned)((n + 255) / 256), ne);
+  if (ap.hw > 0.0 || ap.hh > 0.0)
+    hipLaunchKernelGGL(k_incident<true>, grid, dim3(256), 0, st, g.dim, g.nx, g.ny, g.nz, g.dx, k, ne, exyz, ap, P0);
+  else
+    hipLaunchKernelGGL(k_incident<false>, grid, dim3(256), 0, st, g.dim, g.nx, g.ny, g.nz, g.dx, k, ne, exyz, ap, P0);
   FWI_LAUNCH_CHECK();
 }
 
