@@ -98,7 +98,8 @@ __host__ __device__ inline void bessel01(double x, double* j0, double* j1, doubl
 // H0^(1)(x) = J0 + i Y0 of real x > 0 for the field kernels, which evaluate it
 // once per grid point and element (bessel01's recurrence of about x + 40 steps
 // and its term-by-term expansion bound them: 221 us per frequency at 256^2 with
-// 64 elements, where the stores take 14; 25 with the forms below).
+// 64 elements, where the stores take 14; 36 with the forms below, bound by
+// their FP64 arithmetic).
 //  * x < 4: J0 and the regular part Y0 - (2/pi) ln(x/2) J0 as polynomials in x^2;
 //  * x >= 4: H0 = sqrt(2/(pi x)) (P + i Q/x) e^{i (x - pi/4)}, P and Q as
 //    polynomials in 1/x^2 on [4, 8] and [8, inf).

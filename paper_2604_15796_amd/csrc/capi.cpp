@@ -38,11 +38,21 @@ thread_local int tl_force_variant = -1;
 thread_local int tl_force_wide = 0;
 thread_local int tl_xy_off = 0;
 
+// Built-in tiles, from timings of every variant on an MI355X (us per launch;
+// batches that fill the device):
+//  * convolution, complex128: (8, 256) against (16, 256): L 64 40 / 31, 96 139 /
+//    126, 128 233 / 212, 192 1855 / 1466, equal elsewhere (the column counts
+//    coincide from 512 on); 512: (8, 512 threads) 549 against 592 (twice the
+//    waves in flight).
+//  * convolution, complex64: (16, 512) is the fastest from 128 on except 192
+//    (the radix 16 x 12 plan needs 12 points per thread); L 48, 64, 96:
+//    (16, 256) 10.5, 19, 46 against 12.5, 25, 57.
+//  * elevation passes: complex128 from 128 on (16, 512): 256 845 against 925.
 int default_variant(int pass, bool dbl, int L) {
   if (pass == PK_ROW_FWD || pass == PK_ROW_INV) return 0;  // 2048 points per workgroup
-  if (pass == PK_CONV && L == 192) return 1;                 // (16, 256): the radix 16 x 12 plan
-  if (pass == PK_CONV && !dbl) return 2;                     // (16, 512) columns, threads
-  return dbl ? 0 : 1;                                        // (8, 256) / (16, 256)
+  if (pass == PK_CONV && dbl) return L == 512 ? 2 : 1;
+  if (pass == PK_CONV) return L == 48 || L == 64 || L == 96 || L == 192 ? 1 : 2;
+  return dbl ? (L >= 128 ? 2 : 0) : 1;
 }
 
 // Fastest variant by measured time; another variant replaces the default only

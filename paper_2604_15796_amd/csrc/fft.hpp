@@ -37,15 +37,18 @@ __device__ __forceinline__ auto stage_load(Src& src, int line, int pb, int ro, i
 // least big_ppt(L) points per thread, radices 32/16/12 with fewer stages
 // (fewer LDS exchanges and barriers, fewer twiddled points). Length 192 has
 // a 16 x 12 plan for the strided (line-fastest) tiles only; length 768 an
-// 8 x 8 x 12 plan (three stages instead of 8 x 8 x 4 x 3).
+// 8 x 8 x 12 plan (three stages instead of 8 x 8 x 4 x 3), length 1024 a
+// 16 x 8 x 8 plan (three stages instead of 8 x 8 x 4 x 4: the convolution of
+// 192 planes of 512^2 1256 -> 1138 us in complex128, 631 -> 588 in complex64;
+// two radix-32 stages at 32 points per thread take 1272 and 619).
 __host__ __device__ constexpr int big_ppt(int L, bool lf = true) {
-  return L == 512 || L == 1024 ? 32
-       : (L == 128 || L == 256) ? 16
+  return L == 512 ? 32
+       : (L == 128 || L == 256 || L == 1024) ? 16
        : L == 768 ? 12
        : (L == 192 && lf) ? 12 : 1 << 30;
 }
 __host__ __device__ constexpr int plan_stages(int L, bool big = false) {
-  return big ? (L == 768 ? 3 : 2)
+  return big ? (L == 768 || L == 1024 ? 3 : 2)
        : L == 32 || L == 48 || L == 64 ? 2
        : L == 96 || L == 128 || L == 192 || L == 256 || L == 384 || L == 512 ? 3
        : L == 768 || L == 1024 ? 4 : 0;
@@ -57,7 +60,7 @@ __host__ __device__ constexpr int plan_radix(int L, int s, bool big = false) {
               : L == 256 ? 16
               : L == 512 ? (s == 0 ? 16 : 32)
               : L == 768 ? (s == 2 ? 12 : 8)
-              : L == 1024 ? 32 : 0)
+              : L == 1024 ? (s == 0 ? 16 : 8) : 0)
        : s == 0 ? 8
        : L == 32 ? 4
        : L == 48 ? 6
@@ -320,14 +323,22 @@ struct LineCfg {
   static constexpr int L = L_, NL = NL_, NT = NT_;
   static constexpr bool LF = LF_;
   static constexpr bool PAD = !LF || NL * (int)sizeof(cplx<T>) < 128;
-  static constexpr int LP = PAD ? L + L / 8 : L;  // padded line length (points)
+  // log2 of the points between two padding elements (rows); complex128 lines of
+  // length 768 in tiles of 64-byte rows have one row per 16 points, so that
+  // three workgroups of 52 KB fit a compute unit's LDS instead of two (two-way
+  // conflicts in the first stage's stores): 1490 -> 1370 us for 384 planes of
+  // 384^2. In complex64 the registers hold that tile to two workgroups anyway
+  // and the conflicts cost 9%.
+  static constexpr int PSH = LF && L == 768 && sizeof(T) == 8 && NL == 4 ? 4 : 3;
+  static constexpr int LP = PAD ? L + (L >> PSH) : L;  // padded line length (points)
   static constexpr bool BIG = NL * L / NT >= big_ppt(L, LF);  // radix-32/16/12 plan
   static constexpr int LDS_ELEMS = NL * LP;
-  __device__ static __forceinline__ int pad(int p) { return PAD ? p + (p >> 3) : p; }
+  __device__ static __forceinline__ int pad(int p) { return PAD ? p + (p >> PSH) : p; }
   __device__ static __forceinline__ int lds(int line, int p) { return LF ? pad(p) * NL + line : line * LP + pad(p); }
   // LDS index of point pb + ro, where ro is a compile-time offset and (for a
   // padded layout) ro or pb is a multiple of 8: the padding term splits and ro
-  // becomes an immediate offset of the LDS instruction.
+  // becomes an immediate offset of the LDS instruction (with one row per 16
+  // points too: the other summand is then below 8, or ro a multiple of 16).
   __device__ static __forceinline__ int lds(int line, int pb, int ro) {
     return lds(line, pb) + pad(ro) * (LF ? NL : 1);
   }
