@@ -85,17 +85,28 @@ int padded_length(int n) {
     if (kLengths[i] >= 2 * n) return kLengths[i];
   return 0;
 }
+int op_length(int n) {
+  if (n < 1) return 0;
+  for (int L : kOpLengths)
+    if (L >= 2 * n) return L;
+  return 0;
+}
+int op_depth_length(int n) {
+  const int L = op_length(n);
+  return L == 216 ? 256 : L;
+}
+static int op_index(int L) {
+  for (int i = 0; i < kNumOpLengths; ++i)
+    if (kOpLengths[i] == L) return i;
+  throw Error(FWI_E_UNSUPPORTED, "no twiddles for length " + std::to_string(L));
+}
 template <>
 const c128* Twiddles::get<double>(int L) const {
-  const int i = length_index(L);
-  if (i < 0) throw Error(FWI_E_UNSUPPORTED, "no twiddles for length " + std::to_string(L));
-  return d64[i];
+  return d64[op_index(L)];
 }
 template <>
 const c64* Twiddles::get<float>(int L) const {
-  const int i = length_index(L);
-  if (i < 0) throw Error(FWI_E_UNSUPPORTED, "no twiddles for length " + std::to_string(L));
-  return d32[i];
+  return d32[op_index(L)];
 }
 
 }  // namespace fwi
@@ -381,20 +392,26 @@ int validate_opts(const fwi_solve_opts* o, std::string& msg) {
   return FWI_OK;
 }
 
-Geo make_geo(const fwi_problem* p) {
+// The grid with the padded lengths that `len` (depth axis: `depth_len`) gives.
+Geo make_geo(const fwi_problem* p, int (*len)(int), int (*depth_len)(int)) {
   Geo g;
   g.dim = p->dim;
   g.nx = p->nx;
   g.ny = p->dim == 3 ? p->ny : 1;
   g.nz = p->nz;
-  g.Lx = padded_length(g.nx);
-  g.Ly = p->dim == 3 ? padded_length(g.ny) : 1;
-  g.Lz = padded_length(g.nz);
+  g.Lx = len(g.nx);
+  g.Ly = p->dim == 3 ? len(g.ny) : 1;
+  g.Lz = depth_len(g.nz);
   g.dx = p->dx;
   g.c0 = p->c0;
   g.alpha0 = p->alpha0;
   g.xy = xy_applies(g);
   return g;
+}
+// The operator's grid (the fused lateral-elevation passes know the ABI's
+// padded lengths only).
+Geo make_geo(const fwi_problem* p) {
+  return tl_xy_off ? make_geo(p, op_length, op_depth_length) : make_geo(p, padded_length, padded_length);
 }
 
 // 1 / (kappa0 rho0) of a problem's background (c0^2 when lossless)
@@ -431,25 +448,38 @@ std::string problem_key(const fwi_problem* p) {
 }
 
 // ------------------------------------------------------------ twiddles ---
+// All tables in one allocation, every length's start a multiple of 16 values.
 void make_twiddles(fwi_ctx* c) {
-  for (int li = 0; li < kNumLengths; ++li) {
-    const int L = kLengths[li];
-    std::vector<c128> h64(L);
-    std::vector<c64> h32(L);
-    for (int m = 0; m < L; ++m) {
+  size_t off[kNumOpLengths + 1] = {};
+  for (int i = 0; i < kNumOpLengths; ++i) off[i + 1] = off[i] + (kOpLengths[i] + 15) / 16 * 16;
+  const size_t tot = off[kNumOpLengths];
+  std::vector<char> h(tot * (sizeof(c128) + sizeof(c64)));
+  c128* h64 = reinterpret_cast<c128*>(h.data());
+  c64* h32 = reinterpret_cast<c64*>(h.data() + tot * sizeof(c128));
+  for (int i = 0; i < kNumOpLengths; ++i) {
+    const int L = kOpLengths[i];
+    // the first quarter; the others are it turned by -i (every length is a
+    // multiple of 4)
+    for (int m = 0; m < L / 4; ++m) {
       const long double ang = -2.0L * 3.141592653589793238462643383279502884L * (long double)m / (long double)L;
-      h64[m] = mk((double)cosl(ang), (double)sinl(ang));
-      h32[m] = mk((float)cosl(ang), (float)sinl(ang));
+      const long double cs = cosl(ang), sn = sinl(ang);
+      c128* w64 = h64 + off[i] + m;
+      c64* w32 = h32 + off[i] + m;
+      w64[0] = mk((double)cs, (double)sn);
+      w32[0] = mk((float)cs, (float)sn);
+      for (int q = 1; q < 4; ++q) {
+        w64[q * L / 4] = mul_i(w64[(q - 1) * L / 4], -1);
+        w32[q * L / 4] = mul_i(w32[(q - 1) * L / 4], -1);
+      }
     }
-    void *p64 = nullptr, *p32 = nullptr;
-    FWI_HIP(hipMalloc(&p64, sizeof(c128) * L));
-    c->tw_allocs.push_back(p64);
-    FWI_HIP(hipMalloc(&p32, sizeof(c64) * L));
-    c->tw_allocs.push_back(p32);
-    FWI_HIP(hipMemcpy(p64, h64.data(), sizeof(c128) * L, hipMemcpyHostToDevice));
-    FWI_HIP(hipMemcpy(p32, h32.data(), sizeof(c64) * L, hipMemcpyHostToDevice));
-    c->tw.d64[li] = (const c128*)p64;
-    c->tw.d32[li] = (const c64*)p32;
+  }
+  void* d = nullptr;
+  FWI_HIP(hipMalloc(&d, h.size()));
+  c->tw_allocs.push_back(d);
+  FWI_HIP(hipMemcpy(d, h.data(), h.size(), hipMemcpyHostToDevice));
+  for (int i = 0; i < kNumOpLengths; ++i) {
+    c->tw.d64[i] = reinterpret_cast<const c128*>(d) + off[i];
+    c->tw.d32[i] = reinterpret_cast<const c64*>(reinterpret_cast<const char*>(d) + tot * sizeof(c128)) + off[i];
   }
 }
 
@@ -2304,9 +2334,21 @@ int fwi_green_spectrum(fwi_ctx* c, const fwi_problem* p, int l, void* out) {
     if (rc) throw Error(rc, msg);
     if (!out || l < 0 || l >= p->nf) throw Error(FWI_E_INVAL, "bad arguments");
     ensure_cache(c, p);
-    const long np = c->pc.g.npad();
-    launch_copy_c128(np, c->pc.ghat64 + (long)l * np, (c128*)out, c->stream);
-    FWI_HIP(hipStreamSynchronize(c->stream));
+    const Geo pub = make_geo(p, padded_length, padded_length);
+    const long np = pub.npad();
+    if (pub.Lx == c->pc.g.Lx && pub.Ly == c->pc.g.Ly && pub.Lz == c->pc.g.Lz) {
+      launch_copy_c128(np, c->pc.ghat64 + (long)l * np, (c128*)out, c->stream);
+      FWI_HIP(hipStreamSynchronize(c->stream));
+      return FWI_OK;
+    }
+    // the operator's spectra have other lengths: this one on the ABI's grid
+    c128* table = nullptr;
+    FWI_HIP(hipMalloc((void**)&table, sizeof(c128) * 2 * np));
+    launch_green_table(pub, c->pc.k[l], table, c->stream);
+    launch_fft_full(pub, c->tw, table, table + np, (c128*)out, c->stream);
+    const hipError_t e = hipStreamSynchronize(c->stream);
+    FWI_HIP(hipFree(table));
+    FWI_HIP(e);
     return FWI_OK;
   });
 }
@@ -2317,7 +2359,7 @@ int fwi_fft_padded(fwi_ctx* c, const fwi_problem* p, int precision, const void* 
     int rc = validate_problem(p, msg);
     if (rc) throw Error(rc, msg);
     if (!in || !out) throw Error(FWI_E_INVAL, "bad arguments");
-    const Geo g = make_geo(p);
+    const Geo g = make_geo(p, padded_length, padded_length);
     const size_t es = precision == FWI_FP32_REFINE ? sizeof(c64) : sizeof(c128);
     Arena dry;
     dry.take<char>(es * g.u1());
@@ -2528,7 +2570,7 @@ int fwi_autotune(fwi_ctx* c, const fwi_problem* p, int precision, int B, int rep
     for (int k = 0; k < KC_COUNT; ++k) {
       if (kinds[k] < 0 || k == KC_Y_INV) continue;
       const double* tv = k == KC_Y_FWD ? strided_sum : t[k];
-      if (tv[0] == 0.0) continue;
+      if (tv[0] == 0.0 || length_index(lens[k]) < 0) continue;  // one tile only
       c->tune.v[kinds[k]][dbl ? 1 : 0][length_index(lens[k])] =
           (signed char)pick_variant(tv, default_variant(kinds[k], dbl, lens[k]));
     }

@@ -11,8 +11,8 @@
 // global memory directly (cropping is a store predicate), so a pass costs one
 // read and one write of its data in HBM and S-1 LDS exchanges in between.
 //
-// Lengths are 2^a 3^b (32 ... 1024) with radices 8, 6, 4, 3, or 32, 16 and 12
-// for tiles with many points per thread; every plan starts with a radix of at
+// Lengths are 2^a 3^b 5^c (32 ... 1024) with radices 3 to 10 and 12, or 32, 16 and
+// 12 for tiles with many points per thread; every plan starts with a radix of at
 // least 8, which makes the zero half of a padded input a whole set of
 // predicated-off loads, and the inverse plan is the reverse of the forward one.
 #pragma once
@@ -33,7 +33,7 @@ __device__ __forceinline__ auto stage_load(Src& src, int line, int pb, int ro, i
 }
 
 // ---------------------------------------------------------------- plans ---
-// Two plan families: radices 8/6/4/3 (any tile), and for tiles holding at
+// Two plan families: radices up to 12 (any tile), and for tiles holding at
 // least big_ppt(L) points per thread, radices 32/16/12 with fewer stages
 // (fewer LDS exchanges and barriers, fewer twiddled points). Length 192 has
 // a 16 x 12 plan for the strided (line-fastest) tiles only; length 768 an
@@ -49,9 +49,8 @@ __host__ __device__ constexpr int big_ppt(int L, bool lf = true) {
 }
 __host__ __device__ constexpr int plan_stages(int L, bool big = false) {
   return big ? (L == 768 || L == 1024 ? 3 : 2)
-       : L == 32 || L == 48 || L == 64 ? 2
-       : L == 96 || L == 128 || L == 192 || L == 256 || L == 384 || L == 512 ? 3
-       : L == 768 || L == 1024 ? 4 : 0;
+       : L == 32 || L == 48 || L == 64 || L == 72 || L == 80 ? 2
+       : L == 768 || L == 1024 ? 4 : 3;
 }
 __host__ __device__ constexpr int plan_radix(int L, int s, bool big = false) {
   // forward plan, stage s
@@ -72,7 +71,18 @@ __host__ __device__ constexpr int plan_radix(int L, int s, bool big = false) {
        : L == 384 ? (s == 1 ? 8 : 6)
        : L == 512 ? 8
        : L == 768 ? (s == 1 ? 8 : s == 2 ? 4 : 3)
-       : L == 1024 ? (s == 1 ? 8 : 4) : 0;
+       : L == 1024 ? (s == 1 ? 8 : 4)
+       : L == 72 ? 9
+       : L == 80 ? 10
+       : L == 144 ? (s == 1 ? 3 : 6)
+       : L == 160 ? (s == 1 ? 4 : 5)
+       : L == 216 ? (s == 1 ? 3 : 9)
+       : L == 288 ? 6
+       : L == 320 ? (s == 1 ? 8 : 5)
+       : L == 432 ? (s == 1 ? 9 : 6)
+       : L == 576 ? (s == 1 ? 8 : 9)
+       : L == 640 ? (s == 1 ? 8 : 10)
+       : L == 864 ? (s == 1 ? 9 : 12) : 0;
 }
 // Twiddle power tables (convolution passes): a twiddled stage with radix R
 // stores the powers w^1 .. w^(R-1) of each butterfly class k < Ns in a row of
@@ -148,6 +158,58 @@ __device__ __forceinline__ void dft(cplx<T>* v, int sgn) {
     v[4] = e[1] - t1;
     v[2] = e[2] + t2;
     v[5] = e[2] - t2;
+  } else if constexpr (R == 5) {
+    const T c1 = (T)0.30901699437494742410, c2 = (T)-0.80901699437494742410;  // cos 72, cos 144
+    const T s1 = (T)0.95105651629515357212, s2 = (T)0.58778525229247312917;   // sin 72, sin 144
+    const cplx<T> t1 = v[1] + v[4], t2 = v[2] + v[3], t3 = v[1] - v[4], t4 = v[2] - v[3];
+    const cplx<T> a1 = mk(v[0].x + c1 * t1.x + c2 * t2.x, v[0].y + c1 * t1.y + c2 * t2.y);
+    const cplx<T> a2 = mk(v[0].x + c2 * t1.x + c1 * t2.x, v[0].y + c2 * t1.y + c1 * t2.y);
+    const cplx<T> b1 = mul_i(mk(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y), sgn);
+    const cplx<T> b2 = mul_i(mk(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y), sgn);
+    v[0] = v[0] + t1 + t2;
+    v[1] = a1 + b1;
+    v[4] = a1 - b1;
+    v[2] = a2 + b2;
+    v[3] = a2 - b2;
+  } else if constexpr (R == 9) {
+    // 9 = 3 x 3: n = 3 n1 + n2, k = k1 + 3 k2, twiddles exp(sgn 2 pi i n2 k1 / 9)
+    cplx<T> a[3][3];
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < 3; ++n1) a[n2][n1] = v[3 * n1 + n2];
+      dft<3>(a[n2], sgn);
+    }
+    const T g = (T)sgn;
+    const cplx<T> w1 = mk((T)0.76604444311897803520, g * (T)0.64278760968653932632);   // 40 degrees
+    const cplx<T> w2 = mk((T)0.17364817766693034885, g * (T)0.98480775301220805937);   // 80
+    const cplx<T> w4 = mk((T)-0.93969262078590838405, g * (T)0.34202014332566873304);  // 160
+    a[1][1] = a[1][1] * w1;
+    a[1][2] = a[1][2] * w2;
+    a[2][1] = a[2][1] * w2;
+    a[2][2] = a[2][2] * w4;
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) {
+      cplx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+      dft<3>(b, sgn);
+#pragma unroll
+      for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = b[k2];
+    }
+  } else if constexpr (R == 10) {
+    // prime-factor split 10 = 2 x 5: input n = 5 n1 + 2 n2, output
+    // k = 5 k1 + 6 k2 (mod 10), no twiddles in between
+    cplx<T> a[2][5];
+#pragma unroll
+    for (int n1 = 0; n1 < 2; ++n1) {
+#pragma unroll
+      for (int n2 = 0; n2 < 5; ++n2) a[n1][n2] = v[(5 * n1 + 2 * n2) % 10];
+      dft<5>(a[n1], sgn);
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < 5; ++k2) {
+      v[(6 * k2) % 10] = a[0][k2] + a[1][k2];
+      v[(5 + 6 * k2) % 10] = a[0][k2] - a[1][k2];
+    }
   } else if constexpr (R == 12) {
     // prime-factor split 12 = 3 x 4 (Good-Thomas): input n = 4 n1 + 3 n2,
     // output k = 4 k1 + 9 k2 (mod 12), i.e. k = k1 mod 3 and k = k2 mod 4, so
@@ -276,7 +338,7 @@ __device__ __forceinline__ void apply_twiddles(cplx<T>* v, cplx<T> w1) {
   }
 }
 
-// Radix 12 / 16 / 32: w^r = (w^8)^(r div 8) w^(r mod 8) from two table values.
+// Radix 9 to 32: w^r = (w^8)^(r div 8) w^(r mod 8) from two table values.
 template <int R, typename T>
 __device__ __forceinline__ void apply_twiddles_big(cplx<T>* v, cplx<T> w1, cplx<T> w8) {
   cplx<T> p[8];

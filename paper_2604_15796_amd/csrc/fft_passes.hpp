@@ -650,7 +650,9 @@ void launch_strided_k(const StridedArgs<T>& a, dim3 grid, hipStream_t st) {
   constexpr int NTV = col_nt<V>();
   FWI_TIMED_LAUNCH((k_strided<T, L, NL, NTV, MODE, HALF, WIDE>), grid, dim3(NTV), 0, st, a);
 }
-template <typename T, int L, int V>
+// CONV: 1 the convolution only, 0 the transforms only, -1 both (keeps the tiles of
+// the lengths with one tile per pass from being built for the other pass).
+template <typename T, int L, int V, int CONV = -1>
 void launch_strided_v(const StridedArgs<T>& a, long planes, int mode, hipStream_t st) {
   constexpr int NL = col_nl<T, L, V>();
   if (planes == 0) return;
@@ -666,40 +668,45 @@ void launch_strided_v(const StridedArgs<T>& a, long planes, int mode, hipStream_
   const bool wide = span > kNarrowMax || tl_force_wide;
   const bool hin = 2 * a.lin <= L, hout = 2 * a.lout <= L;
   if (mode == 2) {
-    if (!hin || !hout) throw Error(-6, "convolution lines must be zero-padded to twice their length");
-    // 64-bit path: one tile variant, planes along y
-    if (wide) {
-      args.tile_major = 0;
-      launch_strided_k<T, L, 0, 2, true, true>(args, dim3((a.nlines + col_nl<T, L, 0>() - 1) / col_nl<T, L, 0>(), grid.y), st);
-    } else if (args.tile_major) {
-      if (CONV_RPW != 1) throw Error(-6, "tile-major convolution takes one plane per workgroup");
-      const long items = (long)grid.x * planes;
-      if (items > 0x7fffffffL) throw Error(-6, "too many convolution work items for one launch");
-      launch_strided_k<T, L, V, 2, true, false>(args, dim3((unsigned)items), st);
-    } else {
-      launch_strided_k<T, L, V, 2, true, false>(args, grid, st);
+    if constexpr (CONV != 0) {
+      if (!hin || !hout) throw Error(-6, "convolution lines must be zero-padded to twice their length");
+      // 64-bit path: one tile variant, planes along y
+      if (wide) {
+        args.tile_major = 0;
+        const dim3 g0((a.nlines + col_nl<T, L, 0>() - 1) / col_nl<T, L, 0>(), grid.y);
+        launch_strided_k<T, L, 0, 2, true, true>(args, g0, st);
+      } else if (args.tile_major) {
+        if (CONV_RPW != 1) throw Error(-6, "tile-major convolution takes one plane per workgroup");
+        const long items = (long)grid.x * planes;
+        if (items > 0x7fffffffL) throw Error(-6, "too many convolution work items for one launch");
+        launch_strided_k<T, L, V, 2, true, false>(args, dim3((unsigned)items), st);
+      } else {
+        launch_strided_k<T, L, V, 2, true, false>(args, grid, st);
+      }
     }
-  } else if (mode == 0) {
-    if (wide) {
-      const dim3 g0((a.nlines + col_nl<T, L, 0>() - 1) / col_nl<T, L, 0>(), grid.y);
-      if (hin) {
-        launch_strided_k<T, L, 0, 0, true, true>(args, g0, st);
+  } else if constexpr (CONV != 1) {
+    const dim3 g0((a.nlines + col_nl<T, L, 0>() - 1) / col_nl<T, L, 0>(), grid.y);
+    if (mode == 0) {
+      if (wide) {
+        if (hin) {
+          launch_strided_k<T, L, 0, 0, true, true>(args, g0, st);
+        } else if constexpr (sizeof(T) == 8) {
+          launch_strided_k<T, L, 0, 0, false, true>(args, g0, st);
+        } else {
+          throw Error(-6, "complex64 strided transforms need zero-padded lines");
+        }
+      } else if (hin) {
+        launch_strided_k<T, L, V, 0, true, false>(args, grid, st);
       } else if constexpr (sizeof(T) == 8) {
-        launch_strided_k<T, L, 0, 0, false, true>(args, g0, st);
+        launch_strided_k<T, L, V, 0, false, false>(args, grid, st);
       } else {
         throw Error(-6, "complex64 strided transforms need zero-padded lines");
       }
-    } else if (hin) {
-      launch_strided_k<T, L, V, 0, true, false>(args, grid, st);
-    } else if constexpr (sizeof(T) == 8) {
-      launch_strided_k<T, L, V, 0, false, false>(args, grid, st);
     } else {
-      throw Error(-6, "complex64 strided transforms need zero-padded lines");
+      if (!hout) throw Error(-6, "inverse strided transform must crop to half a line");
+      if (wide) launch_strided_k<T, L, 0, 1, true, true>(args, g0, st);
+      else launch_strided_k<T, L, V, 1, true, false>(args, grid, st);
     }
-  } else {
-    if (!hout) throw Error(-6, "inverse strided transform must crop to half a line");
-    if (wide) launch_strided_k<T, L, 0, 1, true, true>(args, dim3((a.nlines + col_nl<T, L, 0>() - 1) / col_nl<T, L, 0>(), grid.y), st);
-    else launch_strided_k<T, L, V, 1, true, false>(args, grid, st);
   }
   FWI_LAUNCH_CHECK();
 }
@@ -727,18 +734,49 @@ void launch_strided_v(const StridedArgs<T>& a, long planes, int mode, hipStream_
     default: throw Error(-6, "unsupported FFT length " + std::to_string(L)); \
   }
 
+// Operator lengths between the tuned ones: one tile per pass (rows of 2048
+// points; elevation passes (16, 256), complex128 (8, 256) and from 128 points on
+// (16, 512)). The convolution takes (16, 256) and for 320 to 640 complex64 points
+// (16, 512); the other tile costs, us per launch: 144 19 against 16, 288 30
+// against 28, 432 75 against 64, 576 60 against 53, 640 74 against 69, 864 249
+// against 185.
+#define FWI_OP_LENGTHS(X) X(72) X(80) X(144) X(160) X(216) X(288) X(320) X(432) X(576) X(640) X(864)
+template <typename T>
+constexpr int op_conv_variant(int L) {
+  return sizeof(T) == 4 && L >= 320 && L <= 640 ? 2 : 1;
+}
+template <typename T>
+constexpr int op_strided_variant(int L) {
+  return sizeof(T) == 4 ? 1 : L >= 128 ? 2 : 0;
+}
+
 template <typename T>
 void strided_call(int L, const StridedArgs<T>& a, long planes, int mode, hipStream_t st) {
+#define FWI_X(LL)                                                                              \
+  case LL:                                                                                     \
+    if (mode == 2) launch_strided_v<T, LL, op_conv_variant<T>(LL), 1>(a, planes, mode, st);    \
+    else launch_strided_v<T, LL, op_strided_variant<T>(LL), 0>(a, planes, mode, st);           \
+    return;
+  switch (L) { FWI_OP_LENGTHS(FWI_X) }
+#undef FWI_X
   const int v = tune_variant(mode == 2 ? PK_CONV : PK_STRIDED, sizeof(T) == 8, L);
   FWI_LENGTHS(launch_strided_v, L, v, a, planes, mode, st);
 }
 template <typename T>
 void row_fwd_call(int L, const RowFwdArgs<T>& a, hipStream_t st) {
+#define FWI_X(LL) \
+  case LL: launch_row_fwd_v<T, LL, 0>(a, st); return;
+  switch (L) { FWI_OP_LENGTHS(FWI_X) }
+#undef FWI_X
   const int v = tune_variant(PK_ROW_FWD, sizeof(T) == 8, L);
   FWI_LENGTHS(launch_row_fwd_v, L, v, a, st);
 }
 template <typename T>
 void row_inv_call(int L, const RowInvArgs<T>& a, int epi, hipStream_t st) {
+#define FWI_X(LL) \
+  case LL: launch_row_inv_v<T, LL, 0>(a, epi, st); return;
+  switch (L) { FWI_OP_LENGTHS(FWI_X) }
+#undef FWI_X
   const int v = tune_variant(PK_ROW_INV, sizeof(T) == 8, L);
   FWI_LENGTHS(launch_row_inv_v, L, v, a, epi, st);
 }
@@ -749,6 +787,10 @@ void row_inv_nl_v(int& nl) {
 }
 template <typename T>
 int row_inv_nl(int L) {
+#define FWI_X(LL) \
+  case LL: return row_nl<T, LL, 0>();
+  switch (L) { FWI_OP_LENGTHS(FWI_X) }
+#undef FWI_X
   const int v = tune_variant(PK_ROW_INV, sizeof(T) == 8, L);
   int nl = 0;
   FWI_LENGTHS(row_inv_nl_v, L, v, nl);

@@ -70,10 +70,20 @@ inline void prof_end(int cls, hipStream_t st, double per_rhs, double fixed, bool
   if (tl_prof) tl_prof->end(cls, st, per_rhs, fixed, masked, B);
 }
 
-// Supported FFT lengths (padded axis sizes): 2^a 3^b from 32 to 1024.
+// Padded FFT lengths of the ABI (fwi_padded_length; the grids of the spectrum
+// and FFT diagnostics and the rows of the tuning table): 2^a and 3 2^a from 32
+// to 1024.
 constexpr int kNumLengths = 11;
 constexpr int kLengths[kNumLengths] = {32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
-int length_index(int L);          // -1 if unsupported
+int length_index(int L);          // -1 if not one of them
+// Lengths the operator pads to: those and 9/8, 5/4 and 27/16 of a power of two
+// between them, so that at most a fifth of a line is padding beyond 2n (a half
+// with the lengths above alone: 36 cells were padded to 96, 200 to 512). The
+// linear convolution does not depend on the length. The lengths in between
+// have one tile per pass (no tuning).
+constexpr int kNumOpLengths = 22;
+constexpr int kOpLengths[kNumOpLengths] = {32,  48,  64,  72,  80,  96,  128, 144, 160, 192, 216,
+                                           256, 288, 320, 384, 432, 512, 576, 640, 768, 864, 1024};
 
 // Tile variants of the FFT passes, chosen per (pass, precision, length).
 enum PassKind { PK_ROW_FWD = 0, PK_ROW_INV, PK_CONV, PK_STRIDED, PK_COUNT };
@@ -94,12 +104,17 @@ extern thread_local int tl_xy_off;         // 1: no fused lateral-elevation pass
 __host__ __device__ constexpr bool xy_shape(int MX, int HY) { return (MX == 64 && HY == 128) || (MX == 32 && HY == 64); }
 int default_variant(int pass, bool dbl, int L);
 int tune_variant(int pass, bool dbl, int L);
-int padded_length(int n);         // smallest supported L >= 2n, 0 if none
+int padded_length(int n);         // smallest ABI length >= 2n, 0 if none
+// smallest operator length >= 2n, 0 if none; the depth axis (the convolution's)
+// leaves out 216: its convolution takes 36 us where 256 takes 33 (128 planes of
+// 108^2, complex128; 21 against 20 in complex64)
+int op_length(int n);
+int op_depth_length(int n);
 
-// Twiddle tables tw[m] = exp(-2 pi i m / L) for every supported L.
+// Twiddle tables tw[m] = exp(-2 pi i m / L) for every operator length L.
 struct Twiddles {
-  const c128* d64[kNumLengths] = {};
-  const c64* d32[kNumLengths] = {};
+  const c128* d64[kNumOpLengths] = {};
+  const c64* d32[kNumOpLengths] = {};
   template <typename T>
   const cplx<T>* get(int L) const;
 };
