@@ -718,6 +718,7 @@ struct ArnoldiDriver {
   const int* rhs_freq;
   hipStream_t st;
   int B;
+  int ndot = 0;  // parts of the current step that the orthogonalising pass sums itself
   // first pass of step 0 on V_0 (scaled by vscale_0 in the last pass)
   void first_rows() {
     launch_vie_rows<T>(g, tw, B, ks.V, ks.active, mT, s.U1, st, nullptr, nullptr, nullptr, s.U2);
@@ -728,17 +729,29 @@ struct ArnoldiDriver {
     VieDots dots = arnoldi_dots(ks, j);
     launch_vie_tail<T>(g, tw, B, ks.V + (long)j * vs, ks.vscale + (long)j * ks.B, ks.active, ghatT, rhs_freq, s.U1,
                        s.U2, ks.V + (long)(j + 1) * vs, nullptr, EPI_VIE, st, nullptr, nullptr, &dots);
-    int ndot = dots.nparts;
-    if (ndot == 0) {
+    int parts = dots.nparts;
+    if (parts == 0) {
       krylov_dots(ks, j, st);
-      ndot = ks.nblk;
+      parts = ks.nblk;
     }
-    krylov_hsum(ks, j, ndot, st);
+    ndot = fuse_hsum(parts) ? parts : 0;
+    if (!ndot) krylov_hsum(ks, j, parts, st);
   }
+  // The sum of the parts costs a launch of its own (3 to 5 us, its result is
+  // waited for) or 16 bytes per part and vector in every workgroup of the
+  // orthogonalising pass. The latter while the parts are few against the pass's
+  // 2048 points per vector and the launch is short (plane waves 192x160, 3360
+  // workgroups: 1.2% of the gradient; 256^2, 512 right-hand sides: the launch is
+  // 5 us of 800 per step, less than the workgroups' sums).
+  bool fuse_hsum(int parts) const { return !g.xy && parts <= 64 && (long)parts * ks.B <= 4096; }
   // orthogonalise w_{j+1} (and transform it unless this was the last step),
   // then the rotations of column j
   void orth_givens(int j, bool transform) {
-    const OrthIn o = arnoldi_orth(ks, j, s.rowpart, transform);
+    OrthIn o = arnoldi_orth(ks, j, s.rowpart, transform);
+    o.ndot = ndot;
+    o.dotp = ks.dotp;
+    o.vscale = ks.vscale;
+    o.H = ks.H;
     launch_vie_rows<T>(g, tw, B, ks.V + (long)(j + 1) * ks.vstride(), ks.active, mT, s.U1, st, nullptr, &o,
                        nullptr, s.U2);
     krylov_givens(ks, j, s.rowpart, g.nz * g.ny, st);
@@ -1977,7 +1990,14 @@ void apply_operator_in(fwi_ctx* c, const fwi_problem* p, int precision, const vo
   }
   plan(a, rf, mT, U1, U2);
   hipStream_t st = c->stream;
-  FWI_HIP(hipMemcpyAsync(rf, freq_index, sizeof(int) * B, hipMemcpyHostToDevice, st));
+  // one frequency, or a frequency-major batch with equally many vectors each:
+  // the indices follow from two numbers (a kernel argument instead of a copy)
+  int per = 1;
+  while (per < B && freq_index[per] == freq_index[0]) ++per;
+  bool regular = true;
+  for (int b = 0; b < B && regular; ++b) regular = freq_index[b] == freq_index[0] + b / per;
+  if (regular) launch_fill_rfreq(B, per, freq_index[0], rf, st);
+  else FWI_HIP(hipMemcpyAsync(rf, freq_index, sizeof(int) * B, hipMemcpyHostToDevice, st));
   if (precision == FWI_FP32_REFINE) {
     launch_cast_64_32(n, (const c128*)m, (c64*)mT, st);
     launch_vie<float>(g, c->tw, B, (const c64*)x, nullptr, nullptr, (const c64*)mT, c->pc.ghat32, rf, (c64*)U1,

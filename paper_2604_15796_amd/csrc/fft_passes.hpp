@@ -73,6 +73,8 @@ __device__ __forceinline__ bool any_row(const int* s_ok, int nl) {
   return any != 0;
 }
 
+constexpr int kMaxDotVec = 33;  // basis vectors of the largest restart (32) + 1
+
 // ------------------------------------------------------------- row pass 1 ---
 // Input of the first pass: the rows of x as they are, or a combination with
 // basis vectors formed first (see k_row_fwd).
@@ -99,6 +101,12 @@ struct RowFwdArgs {
   cplx<T>* lc_out;       // = x, written
   double* lc_rowpart;    // orthogonalisation / start: |v|^2 per row
   const c128* lc_src;    // start: the right-hand sides
+  int per_rhs;           // workgroups per RHS (0: rows packed across RHS)
+  // orthogonalisation with the sum of the inner-product parts (see OrthIn)
+  int ndot, nB;
+  const c128* dotp;
+  const cplx<T>* vscale;
+  c128* H;
 };
 
 template <typename T, int K>
@@ -129,11 +137,17 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
   __shared__ int s_ok[C::NL];
   __shared__ int s_k[K != RI_PLAIN ? C::NL : 1];
   __shared__ int s_b[K != RI_PLAIN ? C::NL : 1];
-  const long g0 = (long)blockIdx.x * C::NL;
+  __shared__ c128 s_coef[ORTH ? kMaxDotVec : 1];
+  long g0 = (long)blockIdx.x * C::NL, gend = a.nrows;  // the workgroup's first row, end of its rows
+  if (ORTH && a.per_rhs) {
+    const unsigned b = blockIdx.x / (unsigned)a.per_rhs, part = blockIdx.x % (unsigned)a.per_rhs;
+    g0 = (long)b * a.rows_per_rhs + (long)part * C::NL;
+    gend = (long)(b + 1) * a.rows_per_rhs;
+  }
   for (int l = threadIdx.x; l < C::NL; l += NT) {
     const long g = g0 + l;
-    int ok = g < a.nrows;
-    const long gc = ok ? g : a.nrows - 1;  // rows past the end read the last row (not stored)
+    int ok = g < gend;
+    const long gc = ok ? g : gend - 1;  // rows past the end read the last row (not stored)
     const long b = gc / a.rows_per_rhs;
     if (ok && a.active && !a.active[b]) ok = 0;
     const long z = gc - b * a.rows_per_rhs;
@@ -171,6 +185,30 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
     static_assert(ORTH || START || sizeof(T) == 8, "the solution update is complex128");
     using TB = lc_basis_t<T, K>;
     using TA = std::conditional_t<ORTH, T, double>;  // accumulation type
+    if constexpr (ORTH) {
+      if (a.ndot) {
+        // column of H and the coefficients from the parts (one RHS): wave w
+        // sums vectors w, w + 4, ..., each lane a fixed subset of the parts
+        const int lane = threadIdx.x & 63, b = s_b[0];
+        for (int i = threadIdx.x >> 6; i < a.lc_nvec; i += NT / 64) {
+          double r = 0.0, m = 0.0;
+          for (int k = lane; k < a.ndot; k += 64) {
+            const c128 d = a.dotp[((long)b * a.ndot + k) * a.lc_cstride + i];
+            r += d.x;
+            m += d.y;
+          }
+          r = wave_sum(r);
+          m = wave_sum(m);
+          if (lane == 0) {
+            const double sc = (double)a.vscale[(long)i * a.nB + b].x;
+            s_coef[i] = mk(-(r * sc), -(m * sc));
+            if (g0 == (long)b * a.rows_per_rhs)
+              a.H[((long)b * a.lc_cstride + i) * (a.lc_cstride - 1) + a.lc_nvec - 1] = mk(r, m);
+          }
+        }
+        __syncthreads();
+      }
+    }
     // the points the first stage will ask this thread for: slot t, leg r
     constexpr int R0 = stage_radix(L, 0, 0, C::BIG);
     constexpr int NJ = L / R0, NB0 = C::NL * NJ, TT0 = (NB0 + NT - 1) / NT, RIN0 = R0 / 2;
@@ -210,7 +248,7 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
         C::template split<R0>(t, line, j);
         if (line >= C::NL) line = C::NL - 1;
         const bool use = ORTH || i < s_k[line];  // every RHS of an orthogonalisation has nvec vectors
-        const c128 c64 = a.lc_coef[(long)s_b[line] * a.lc_cstride + i];
+        const c128 c64 = ORTH && a.ndot ? s_coef[i] : a.lc_coef[(long)s_b[line] * a.lc_cstride + i];
         const cplx<TA> c = mk((TA)c64.x, (TA)c64.y);
 #pragma unroll
         for (int r = 0; r < RIN0; ++r) {
@@ -306,8 +344,6 @@ struct RowInvArgs {
   int nparts, dstride;
 };
 
-constexpr int kMaxDotVec = 33;  // basis vectors of the largest restart (32) + 1
-
 template <typename T, int L, int NLV, int EPI>
 __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
   using C = LineCfg<T, L, NLV, NT, false>;
@@ -321,10 +357,17 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
   __shared__ double s_part[RESID ? C::NL * NsL : 1];
   if constexpr (RESID)
     for (int i = threadIdx.x; i < C::NL * NsL; i += NT) s_part[i] = 0.0;
-  const long g0 = (long)blockIdx.x * C::NL;
+  // with inner products a workgroup's rows belong to one RHS (nparts per RHS,
+  // the last one ragged); else rows are packed across RHS
+  long g0 = (long)blockIdx.x * C::NL, gend = a.nrows;
+  if constexpr (EPI == EPI_VIE_DOT) {
+    const unsigned b = blockIdx.x / (unsigned)a.nparts, part = blockIdx.x % (unsigned)a.nparts;
+    g0 = (long)b * a.rows_per_rhs + (long)part * C::NL;
+    gend = (long)(b + 1) * a.rows_per_rhs;
+  }
   for (int l = threadIdx.x; l < C::NL; l += NT) {
     const long g = g0 + l;
-    int ok = g < a.nrows;
+    int ok = g < gend;
     const long b = ok ? g / a.rows_per_rhs : 0;
     if (ok && a.active && !a.active[b]) ok = 0;
     s_ok[l] = ok;
@@ -334,7 +377,7 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
   if (!any_row(s_ok, C::NL)) return;  // converged right-hand sides: no traffic
   // rows past the end read the last row and are not stored; epilogue loads
   // use clamped indices so they are not behind the store predicate
-  auto row = [&](int line) { return g0 + line < a.nrows ? g0 + line : a.nrows - 1; };
+  auto row = [&](int line) { return g0 + line < gend ? g0 + line : gend - 1; };
   auto src = [&](int line, int pb, int ro) -> cplx<T> { return a.in[row(line) * L + pb + ro]; };
   auto snk = [&](int line, int pb, int ro, cplx<T> v) {
     const int p = pb + ro;
@@ -366,13 +409,14 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
   if constexpr (EPI == EPI_VIE_DOT) {
     // The workgroup's rows (one RHS, contiguous in y and in every basis
     // vector) were just stored; after the barrier each thread reads back EPD
-    // elements of them and streams the basis vectors over the same elements.
+    // elements of them and streams the basis vectors over the same elements
+    // (two or four vectors at a time cost registers: 1.5% of a 256^2 gradient).
     __syncthreads();
     constexpr int EPD = (C::NL * (L / 2) + NT - 1) / NT;
     const long b0 = g0 / a.rows_per_rhs;
     const int part = (int)((g0 - b0 * a.rows_per_rhs) / C::NL);
     const long base = g0 * a.nout;
-    const int cnt = C::NL * a.nout;
+    const int cnt = (int)(gend - g0 < C::NL ? gend - g0 : C::NL) * a.nout;
     const int t = threadIdx.x;
     double yx[EPD], yy[EPD];
 #pragma unroll
@@ -592,10 +636,15 @@ __global__ void __launch_bounds__(NTV) k_strided(StridedArgs<T> a) {
 
 // ---------------------------------------------------------------- dispatch ---
 template <typename T, int L, int V>
-void launch_row_fwd_v(const RowFwdArgs<T>& a, hipStream_t st) {
+void launch_row_fwd_v(const RowFwdArgs<T>& args, hipStream_t st) {
   constexpr int NL = row_nl<T, L, V>();
-  const unsigned grid = (unsigned)((a.nrows + NL - 1) / NL);
+  RowFwdArgs<T> a = args;
+  unsigned grid = (unsigned)((a.nrows + NL - 1) / NL);
   if (grid == 0) return;
+  if (a.ndot) {  // the coefficients are formed per workgroup: one RHS each
+    a.per_rhs = (a.rows_per_rhs + NL - 1) / NL;
+    grid = (unsigned)(a.nrows / a.rows_per_rhs) * (unsigned)a.per_rhs;
+  }
   if (a.kind != RI_PLAIN) {
     if (2 * a.nin > L) throw Error(-6, "combined row inputs need zero-padded rows");
     if (a.kind == RI_ORTH) {
@@ -626,12 +675,11 @@ void launch_row_inv_v(const RowInvArgs<T>& a, int epi, hipStream_t st) {
   if (grid == 0) return;
   if (2 * a.nout > L) throw Error(-6, "inverse row transform must crop to half a padded row");
   if (epi == EPI_VIE_DOT) {
-    // only when every workgroup's rows belong to one RHS and the parts fit
-    if (a.rows_per_rhs % NL != 0 || a.rows_per_rhs / NL > kMaxDotParts || a.nvec > kMaxDotVec)
-      throw Error(-6, "fused inner products not applicable");
     RowInvArgs<T> b = a;
-    b.nparts = a.rows_per_rhs / NL;
-    FWI_TIMED_LAUNCH((k_row_inv<T, L, NL, EPI_VIE_DOT>), dim3(grid), dim3(NT), 0, st, b);
+    b.nparts = (a.rows_per_rhs + NL - 1) / NL;
+    if (b.nparts > kMaxDotParts || a.nvec > kMaxDotVec) throw Error(-6, "fused inner products not applicable");
+    const unsigned parts = (unsigned)(a.nrows / a.rows_per_rhs) * (unsigned)b.nparts;
+    FWI_TIMED_LAUNCH((k_row_inv<T, L, NL, EPI_VIE_DOT>), dim3(parts), dim3(NT), 0, st, b);
   } else if (epi == EPI_VIE) {
     FWI_TIMED_LAUNCH((k_row_inv<T, L, NL, EPI_VIE>), dim3(grid), dim3(NT), 0, st, a);
   } else if (epi == EPI_COPY) {
@@ -759,7 +807,10 @@ void strided_call(int L, const StridedArgs<T>& a, long planes, int mode, hipStre
     return;
   switch (L) { FWI_OP_LENGTHS(FWI_X) }
 #undef FWI_X
-  const int v = tune_variant(mode == 2 ? PK_CONV : PK_STRIDED, sizeof(T) == 8, L);
+  int v = tune_variant(mode == 2 ? PK_CONV : PK_STRIDED, sizeof(T) == 8, L);
+  // a complex128 convolution too short to give every second compute unit a
+  // 16-column tile takes 8 columns (4 planes of 64^2: 4.2 against 5.2 us)
+  if (mode == 2 && sizeof(T) == 8 && v == 1 && tl_force_variant < 0 && (long)(a.nlines + 15) / 16 * planes < 128) v = 0;
   FWI_LENGTHS(launch_strided_v, L, v, a, planes, mode, st);
 }
 template <typename T>
@@ -868,6 +919,14 @@ void launch_vie_rows(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
     f.lc_cstride = orth->cstride;
     f.lc_out = const_cast<cplx<T>*>(x);
     f.lc_rowpart = orth->rowpart;
+    if (orth->ndot) {
+      if (orth->nvec > kMaxDotVec) throw Error(-6, "too many vectors for the fused coefficient sum");
+      f.ndot = orth->ndot;
+      f.nB = B;
+      f.dotp = orth->dotp;
+      f.vscale = static_cast<const cplx<T>*>(orth->vscale);
+      f.H = orth->H;
+    }
     // w read, nvec basis vectors read, v written, per-row norms (and the x-pass intermediate)
     per_rhs = (2.0 + orth->nvec) * n * es + 8.0 * rows_per_rhs + (orth->transform ? g.u1() * es : 0.0);
   } else if (start) {
@@ -882,6 +941,7 @@ void launch_vie_rows(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
   // the orthogonalising first pass and the orthogonalisation alone are classes of their own
   const int cls = orth ? (orth->transform ? KC_ORTH_FWD : KC_ORTH) : KC_ROW_FWD;
   if constexpr (sizeof(T) == 4) {
+    if (g.xy && f.ndot) throw Error(-6, "the fused lateral-elevation pass takes the coefficients");
     if (g.xy && f.kind != RI_ORTH_ONLY) {
       // fused lateral-elevation pass: the operand straight to the padded
       // spectrum U2 (class-major), no x-pass intermediate
@@ -1058,7 +1118,9 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
   if (dots) {
     dots->nparts = 0;
     const int nl = row_inv_nl<T>(g.Lx);
-    if (epi == EPI_VIE && rows_per_rhs % nl == 0 && rows_per_rhs / nl <= kMaxDotParts &&
+    // (grids of fewer rows than a workgroup holds keep their rows packed)
+    const long parts = (rows_per_rhs + nl - 1) / nl;
+    if (epi == EPI_VIE && (rows_per_rhs >= nl || rows_per_rhs % nl == 0) && parts <= kMaxDotParts &&
         dots->nvec <= kMaxDotVec) {
       epi = EPI_VIE_DOT;
       r.basis = static_cast<const cplx<T>*>(dots->basis);
@@ -1068,7 +1130,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
       r.B = B;
       r.dotp = dots->dotp;
       r.dstride = dots->dstride;
-      dots->nparts = (int)(rows_per_rhs / nl);
+      dots->nparts = (int)parts;
     }
   }
   // per RHS: the x-pass intermediate, then x and y (VIE), or x, rhs, the

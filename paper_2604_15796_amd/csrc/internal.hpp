@@ -148,8 +148,8 @@ enum Epilogue { EPI_VIE = 0, EPI_RESID = 1, EPI_COPY = 2, EPI_RESID32 = 3, EPI_V
 
 // Arnoldi inner products fused into the last pass of an EPI_VIE operator:
 // dotp[b][part][i] = vscale_i,b * sum over the part's rows of conj(V_i) . y,
-// i < nvec, one part per workgroup of the inverse row pass. Done only when
-// every workgroup's rows belong to one RHS and there are at most kMaxDotParts
+// i < nvec, one part per workgroup of the inverse row pass. Done only when a
+// RHS fills a workgroup's rows at least once and there are at most kMaxDotParts
 // parts per RHS; launch_vie reports whether it did them (and `nparts`).
 constexpr int kMaxDotParts = 2048;
 struct VieDots {
@@ -190,6 +190,14 @@ struct OrthIn {
   int cstride = 0;
   double* rowpart = nullptr;    // [B * rows per RHS]
   bool transform = true;
+  // Sum of the inner-product parts fused into the pass (ndot > 0; coef is then
+  // not read): every workgroup sums the ndot parts of its RHS in the order of
+  // krylov_hsum and forms the coefficients in LDS, the first of each RHS stores
+  // column nvec - 1 of H.
+  int ndot = 0;
+  const c128* dotp = nullptr;   // [B][ndot][cstride]
+  const void* vscale = nullptr; // [cstride][B] cplx<T>
+  c128* H = nullptr;            // [B][cstride][cstride - 1]
 };
 
 // First cycle (x_0 = 0, r = b) fused into the first pass: V_0 = b rounded to

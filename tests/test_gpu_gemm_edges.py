@@ -52,3 +52,25 @@ def test_symmetric_jacobian_products_at_tile_edges_vs_oracle(ctx, nx, nz, ne):
     k2 = np.array([O.wavenumber(q, p.c0) ** 2 for q in p.freqs])
     ref = p.dx ** 2 * sum(k2[l] * np.conj(np.sum(f[l] * (np.conj(b[l]) @ f[l]), axis=0)) for l in range(p.nf))
     assert _err(ctx.jacobian_adjoint_apply(p, _dev(f), _dev(b)).cpu().numpy(), ref) < 1e-12
+
+
+@pytest.mark.parametrize("dim,shape,ne", [(2, (37, 50), 3), (2, (5, 200), 2), (2, (64, 33), 5), (3, (11, 9, 20), 3),
+                                          (2, (130, 120), 60)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_solver_with_ragged_rows_vs_oracle(ctx, dim, shape, ne, prec):
+    """Rows per right-hand side that do not fill the row passes' workgroups (or
+    fewer than one), so that the last part of the inner products is ragged; and
+    enough right-hand sides (60) that the coefficient sums are a kernel of their
+    own. Field error bound: the solve's tolerance, 1e-10, times 100."""
+    from paper_2604_15796_amd import fwi
+    nx, nz = shape[-1], shape[0]
+    p = W.small2d(seed=nx + nz, nx=nx, nz=nz, ne=ne, nf=1) if dim == 2 else \
+        W.small3d(seed=nx + nz, nx=nx, ny=shape[1], nz=nz, ne=ne)
+    args = (dim, p.nx, p.ny, p.nz, p.dx, p.c0, p.freqs, p.elems)
+    tx = np.arange(ne) if ne < 10 else np.array([0, 31, 59])
+    _, ref, _ = O.forward(p.c, p.alpha, *args, tx=tx)
+    opts = fwi.SolveOptions(precision=prec, rtol=1e-10, restart=16)
+    _, F, st = ctx.forward(p, torch.as_tensor(p.c).to(DEV), torch.as_tensor(p.alpha).to(DEV), opts, fields=True)
+    got = F.cpu().numpy()[:, tx]
+    err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    assert st["unconverged"] == 0 and err.max() < 1e-8
