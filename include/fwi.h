@@ -176,7 +176,10 @@ void fwi_default_opts(fwi_solve_opts* opts);
 /* Host-only argument check; returns FWI_OK or FWI_E_INVAL / FWI_E_UNSUPPORTED.
  * Elements must lie on z = 0 within the lateral extent; frequencies > 0. */
 int fwi_validate_problem(const fwi_problem* prob);
-/* Padded FFT length used for an axis of n cells (smallest 2^a 3^b >= 2n), 0 if n > 512. */
+/* Padded FFT length of the ABI's grids (fwi_green_spectrum, fwi_fft_padded, the
+ * tuning table) for an axis of n cells: the smallest 2^a or 3 2^a >= 2n, at
+ * least 32; 0 if n > 512. The operator itself may pad to a length between
+ * those (72 to 864), which leaves its results the same. */
 int fwi_padded_length(int n);
 
 /* Workspace bytes an entry point needs (host-only). entry: 0 forward,
@@ -352,7 +355,9 @@ int fwi_solve(fwi_ctx* ctx, const fwi_problem* prob, const void* m, int B, const
 /* Incident fields p0 [ne][n] complex128 of frequency freq_index (Sec. II). */
 int fwi_incident(fwi_ctx* ctx, const fwi_problem* prob, int freq_index, void* out);
 
-/* Green spectrum FFT(k^2 W)/npad on the padded grid [Lz][Ly][Lx] complex128. */
+/* Green spectrum FFT(k^2 W)/npad on the padded grid [Lz][Ly][Lx] complex128
+ * (lengths of fwi_padded_length; computed at the call where the operator pads
+ * an axis to another length). */
 int fwi_green_spectrum(fwi_ctx* ctx, const fwi_problem* prob, int freq_index, void* out);
 
 /* Zero-padded forward FFT of in [nz][ny][nx] into out [Lz][Ly][Lx] (precision
@@ -414,7 +419,8 @@ int fwi_profile_read(const fwi_ctx* ctx, int cls, double* total_ms, long long* l
  * variant of every pass on the device for this problem's grid with B
  * right-hand sides (reps launches each, HIP events) and stores the fastest per
  * (pass, precision, padded length) in the context; a variant replaces the
- * built-in default only if it is at least 2% faster. Later calls use the
+ * built-in default only if it is at least 2% faster. Lengths that are not of
+ * fwi_padded_length have one tile per pass and no entry. Later calls use the
  * table. Report rows: 0 row forward, 1 convolution, 2 row inverse, 3 / 4
  * elevation forward / inverse (3D, tuned on their summed time). */
 typedef struct fwi_tune_report {

@@ -5,7 +5,9 @@
 
 namespace fwi {
 
-// C[l][i][j] = coef[l] sum_n A[l][i][n] w[n] Bm[l][j][n]; part: [nks][nf][ni][nj] scratch
+// C[l][i][j] = coef[l] sum_n A[l][i][n] w[n] Bm[l][j][n]; part: [nks][nf][ni][nj] scratch.
+// With w and one array as A and Bm the product is symmetric in (i, j), and one
+// triangle of it is computed.
 void launch_gemm_nt(int nf, const c128* A, long a_ls, int ni, const c128* w, const c128* Bm, long b_ls, int nj, long n,
                     const c128* coef, c128* part, int nks, c128* C, hipStream_t st);
 // S[l][i][n] = sum_j conj(M[l][i][j]) P[l][j][n]
@@ -35,7 +37,8 @@ void launch_conj_c128(long count, const c128* in, c128* out, hipStream_t st);
 // J^H b in one pass over the receiver fields: S = conj(M) P as in
 // launch_gemm_cn, reduced on the fly with the transmit fields T into
 // conj(k2) conj(T S) partials part [nf * ceil(ni / 64)][n]; launch_grad_sum
-// adds such partials (or those of launch_gradient_accum) in a fixed order.
+// adds such partials (or those of launch_gradient_accum) in a fixed order. With
+// one array as T and P the sum is a quadratic form of M + M^T, half the work.
 int gemm_cn_grad_segments(int nf, int ni);
 void launch_gemm_cn_grad(int nf, const c128* M, int ni, int nj, const c128* P, long p_ls, long n, const c128* T,
                          long t_ls, const c128* k2, c128* part, hipStream_t st);

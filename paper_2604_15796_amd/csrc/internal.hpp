@@ -77,8 +77,9 @@ constexpr int kNumLengths = 11;
 constexpr int kLengths[kNumLengths] = {32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
 int length_index(int L);          // -1 if not one of them
 // Lengths the operator pads to: those and 9/8, 5/4 and 27/16 of a power of two
-// between them, so that at most a fifth of a line is padding beyond 2n (a half
-// with the lengths above alone: 36 cells were padded to 96, 200 to 512). The
+// between them, so that from 64 on at most a quarter of a line is padding beyond
+// 2n, mostly a sixth or less (a third with the lengths above alone: 36 cells
+// were padded to 96, 140 to 384). The
 // linear convolution does not depend on the length. The lengths in between
 // have one tile per pass (no tuning).
 constexpr int kNumOpLengths = 22;
