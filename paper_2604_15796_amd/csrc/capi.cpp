@@ -636,9 +636,9 @@ void plan_solve(Arena& a, const Geo& g, int B, int JM, SolveBufs<T>& s) {
   k.active = a.take<int>(B);
   k.ncol = a.take<int>(B);
   k.iters = a.take<int>(B);
-  k.counters = a.take<int>(4);  // active counts, then the max relative residual: one copy reads both
+  k.counters = a.take<int>(6);  // active counts, then the max relative residual: one copy reads both
   k.maxrel = k.counters ? reinterpret_cast<double*>(k.counters + 2) : nullptr;
-  k.arrive = a.take<unsigned long long>(1);
+  k.arrive = k.counters ? reinterpret_cast<unsigned long long*>(k.counters + 4) : nullptr;
   s.rowpart = a.take<double>((size_t)B * g.nz * g.ny);
   s.U1 = a.take<cplx<T>>((size_t)B * g.u1());
   s.U2 = g.dim == 3 ? a.take<cplx<T>>((size_t)B * g.u2()) : nullptr;
@@ -923,6 +923,8 @@ struct CallBufs {
   c128* r = nullptr;        // [nf][ne][ne]
   c128* gpart = nullptr;    // [nks][nfg][ne][ne] or [nseg][n]
   long gpart_len = 0;       // elements of gpart
+  bool lean = false;        // plan for a small workspace of the caller's (see gemm_splits_lean)
+  int nks = 1;              // most splits of a sampling product that gpart holds
   c128* gacc = nullptr;     // [n]
   double* misfits = nullptr;  // [ngroups * chunks]
   int* rfreq = nullptr;     // [B]
@@ -946,16 +948,28 @@ constexpr int kGradSeg = 16;
 // to 512) when they do not (a 3D grid with one frequency and 64 x 64 outputs
 // is one tile). Below that the count depends on n alone, so that a transmit
 // chunk sums its data in the same order as the whole frequency.
-// gemm_splits_max bounds every launch's count (buffer plans).
+// gemm_splits_max bounds every launch's count (buffer plans). A caller's
+// workspace that has no room for these partials is not refused while it holds
+// one split per 1024 points (gemm_splits_lean) and the call's other buffers:
+// the product then runs on the splits that the buffer holds (64^2 with 64
+// elements and 8 frequencies: 39 MB instead of 71).
 int gemm_splits_max(long n) {
   const long s = std::min<long>(std::max<long>(96, (n + 1023) / 1024), (n + 63) / 64);
   return (int)(s < 1 ? 1 : (s > 512 ? 512 : s));
 }
-int gemm_splits(long n, int nf, int ni, int nj) {
-  if (n < 131072) return gemm_splits_max(n);
+int gemm_splits_lean(long n) { return std::min<long>(gemm_splits_max(n), (n + 1023) / 1024); }
+// splits of a product that takes the workspace for its partials alone
+int product_splits(const fwi_ctx* c, long n, size_t outs) {
+  Arena dry;
+  dry.take<c128>(outs * gemm_splits_max(n));
+  return c->ws_ext && dry.used > c->ws_ext_bytes ? gemm_splits_lean(n) : gemm_splits_max(n);
+}
+// nks: the most that the buffer of the partials holds for the whole problem
+int gemm_splits(long n, int nf, int ni, int nj, int nks) {
+  if (n < 131072) return nks;
   const long units = (long)nf * ((ni + 63) / 64) * ((nj + 63) / 64);
   const long want = std::max<long>(64, (1024 + units - 1) / units);
-  return (int)std::min<long>(gemm_splits_max(n), want);
+  return (int)std::min<long>(nks, want);
 }
 
 // Plans every buffer of an entry point; `entry` as in fwi_workspace_size.
@@ -974,8 +988,9 @@ void plan_call(Arena& a, const fwi_problem* p, const fwi_solve_opts& o, int entr
   cb.data = a.take<c128>(ndata);
   cb.r = a.take<c128>(ndata);
   cb.misfits = a.take<double>((size_t)ngroups * chunks_of(o, p->ne) + 2);
-  const long gp = std::max((long)gemm_splits_max(n) * nfg * p->ne * p->ne, (long)kGradSeg * n);
-  cb.gpart_len = std::max(gp, (long)gemm_splits_max(n) * p->nf * p->ne * p->ne);
+  const int most = gemm_splits_max(n);
+  cb.gpart_len = std::max((long)(cb.lean ? gemm_splits_lean(n) : most) * ndata, (long)kGradSeg * n);
+  cb.nks = (int)std::min<long>(most, cb.gpart_len / ndata);
   cb.gpart = a.take<c128>(cb.gpart_len);
   cb.gacc = a.take<c128>(n);
   if (entry == FWI_ENTRY_ADMM)
@@ -1075,7 +1090,7 @@ struct Runner {
                        (long)ti * n, st);
         solve_rhs<T>(sb, l0, nf, ti, cb.S, F);
         launch_gemm_nt(nf, F, (long)ti * n, ti, cb.m64, P0g, (long)p->ne * n, p->ne, n, pc.coef + l0, cb.gpart,
-                       gemm_splits(n, nf, ti, p->ne), data_out + l0 * nd + (long)t0 * p->ne, st);
+                       gemm_splits(n, nf, ti, p->ne, cb.nks), data_out + l0 * nd + (long)t0 * p->ne, st);
         field_store(fields_out, off, (long)nf * ti * n);
       }
     }
@@ -1101,7 +1116,7 @@ struct Runner {
         launch_gemm_cn(nf, cb.wtx + rows, ti, p->ne, P0g, (long)p->ne * n, n, cb.S, (long)ti * n, st);
         solve_rhs<T>(sb, l0, nf, ti, cb.S, cb.fields);
         launch_gemm_nt(nf, cb.fields, (long)ti * n, ti, cb.m64, P0g, (long)p->ne * n, p->ne, n, pc.coef + l0,
-                       cb.gpart, gemm_splits(n, nf, ti, p->ne), data_out + rows, st);
+                       cb.gpart, gemm_splits(n, nf, ti, p->ne, cb.nks), data_out + rows, st);
         launch_residual((long)nf * ti * p->ne, data_out + rows, dobs + rows, cb.r + rows, cb.misfits + seg, st);
         launch_gemm_cn(nf, cb.r + rows, ti, p->ne, P0g, (long)p->ne * n, n, cb.S, (long)ti * n, st);
         solve_rhs<T>(sb, l0, nf, ti, cb.S, cb.lam);
@@ -1135,7 +1150,7 @@ struct Runner {
         c128* F = field_target(fields_out, off);
         solve_rhs<T>(sb, l0, nf, ni, pc.P0 + off, F);
         launch_gemm_nt(nf, F, (long)ni * n, ni, cb.m64, pc.P0 + (long)l0 * p->ne * n, (long)p->ne * n, p->ne, n,
-                       pc.coef + l0, cb.gpart, gemm_splits(n, nf, ni, p->ne), data_out + l0 * ne2 + (long)i0 * p->ne,
+                       pc.coef + l0, cb.gpart, gemm_splits(n, nf, ni, p->ne, cb.nks), data_out + l0 * ne2 + (long)i0 * p->ne,
                        st);
         field_store(fields_out, off, (long)nf * ni * n);
       }
@@ -1172,7 +1187,7 @@ struct Runner {
           rg = upstream + rows;
         } else {
           launch_gemm_nt(nf, F, (long)ni * n, ni, cb.m64, P0g, (long)p->ne * n, p->ne, n, pc.coef + l0, cb.gpart,
-                         gemm_splits(n, nf, ni, p->ne), data_out + rows, st);
+                         gemm_splits(n, nf, ni, p->ne, cb.nks), data_out + rows, st);
           launch_residual((long)nf * ni * p->ne, data_out + rows, dobs + rows, cb.r + rows, cb.misfits + seg, st);
           rg = cb.r + rows;
         }
@@ -1292,6 +1307,11 @@ void prepare(fwi_ctx* c, Runner& R, SolveBufs<T>& sb, int entry, int B_override 
   CallBufs cbd;
   SolveBufs<T> sbd;
   plan_call<T>(dry, R.p, R.o, entry, cbd, sbd, B_override);
+  if (c->ws_ext && dry.used > c->ws_ext_bytes) {
+    dry = Arena();
+    cbd.lean = R.cb.lean = true;
+    plan_call<T>(dry, R.p, R.o, entry, cbd, sbd, B_override);
+  }
   Arena a;
   bind_workspace(c, a, dry.used);
   plan_call<T>(a, R.p, R.o, entry, R.cb, sb, B_override);
@@ -1437,7 +1457,7 @@ void j_apply(fwi_ctx* c, const fwi_problem* p, const Geo& g, CallBufs& cb, int n
              const c128* a, c128* out) {
   const long n = g.n();
   launch_gemm_nt(p->nf, tx, (long)nt * n, nt, a, rx, (long)p->ne * n, p->ne, n, c->pc.coef, cb.gpart,
-                 gemm_splits(n, p->nf, nt, p->ne),
+                 gemm_splits(n, p->nf, nt, p->ne, cb.nks),
                  out, c->stream);
 }
 
@@ -1784,6 +1804,7 @@ int batch_impl(fwi_ctx* c, int ninst, const fwi_problem* probs, const double* co
     I.grad = grad_out ? (c128*)grad_out[i] : nullptr;
     I.data_out = data_out ? (c128*)data_out[i] : nullptr;
     Arena dry;
+    I.cb.lean = c->ws_ext != nullptr;
     plan_call<T>(dry, I.p, o, FWI_ENTRY_GRADIENT, I.cb, I.sb);
     I.bytes = dry.used;
   }
@@ -1877,7 +1898,7 @@ int batch_impl(fwi_ctx* c, int ninst, const fwi_problem* probs, const double* co
       const int ne = I->p->ne, nf = I->p->nf;
       c128* data = I->data_out ? I->data_out : I->cb.data;
       launch_gemm_nt(nf, I->cb.fields, (long)ne * I->n, ne, I->cb.m64, I->pc->P0, (long)ne * I->n, ne, I->n,
-                     I->pc->coef, I->cb.gpart, gemm_splits(I->n, nf, ne, ne), data, main);
+                     I->pc->coef, I->cb.gpart, gemm_splits(I->n, nf, ne, ne, I->cb.nks), data, main);
       if (gradient) {
         launch_residual((long)nf * ne * ne, data, I->dobs, I->cb.r, I->cb.misfits, main);
         launch_gemm_cn(nf, I->cb.r, ne, ne, I->pc->P0, (long)ne * I->n, I->n, I->cb.S, (long)ne * I->n, main);
@@ -2404,12 +2425,14 @@ int fwi_jacobian_apply(fwi_ctx* c, const fwi_problem* p, const void* fields, con
     ensure_cache(c, p);
     const Geo g = make_geo(p);
     const long n = g.n();
+    CallBufs cb;
+    cb.nks = product_splits(c, n, (size_t)p->nf * p->ne * p->ne);
+    const size_t part = (size_t)cb.nks * p->nf * p->ne * p->ne;
     Arena dry;
-    dry.take<c128>((size_t)gemm_splits_max(n) * p->nf * p->ne * p->ne);
+    dry.take<c128>(part);
     Arena ar;
     bind_workspace(c, ar, dry.used);
-    CallBufs cb;
-    cb.gpart = ar.take<c128>((size_t)gemm_splits_max(n) * p->nf * p->ne * p->ne);
+    cb.gpart = ar.take<c128>(part);
     j_apply(c, p, g, cb, p->ne, (const c128*)fields, (const c128*)fields, (const c128*)a, (c128*)out);
     FWI_HIP(hipStreamSynchronize(c->stream));
     return FWI_OK;
@@ -2462,14 +2485,15 @@ int fwi_jacobian_apply_tx(fwi_ctx* c, const fwi_problem* p, int nt, const void* 
     check_tx_fields(p, nt, tx_fields, rx_fields, a, out);
     ensure_cache(c, p);
     const long n = make_geo(p).n();
-    const size_t part = (size_t)gemm_splits_max(n) * p->nf * nt * p->ne;
+    const int nks = product_splits(c, n, (size_t)p->nf * nt * p->ne);
+    const size_t part = (size_t)nks * p->nf * nt * p->ne;
     Arena dry;
     dry.take<c128>(part);
     Arena ar;
     bind_workspace(c, ar, dry.used);
     c128* gpart = ar.take<c128>(part);
     launch_gemm_nt(p->nf, (const c128*)tx_fields, (long)nt * n, nt, (const c128*)a, (const c128*)rx_fields,
-                   (long)p->ne * n, p->ne, n, c->pc.coef, gpart, gemm_splits(n, p->nf, nt, p->ne), (c128*)out,
+                   (long)p->ne * n, p->ne, n, c->pc.coef, gpart, gemm_splits(n, p->nf, nt, p->ne, nks), (c128*)out,
                    c->stream);
     FWI_HIP(hipStreamSynchronize(c->stream));
     return FWI_OK;

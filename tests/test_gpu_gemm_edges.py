@@ -74,3 +74,30 @@ def test_solver_with_ragged_rows_vs_oracle(ctx, dim, shape, ne, prec):
     got = F.cpu().numpy()[:, tx]
     err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
     assert st["unconverged"] == 0 and err.max() < 1e-8
+
+
+@pytest.mark.parametrize("nx,nz,ne,nf,nbytes", [(64, 64, 64, 8, 39152128), (24, 40, 64, 8, 10118144)])
+def test_forward_in_a_small_caller_workspace(ctx, nx, nz, ne, nf, nbytes):
+    """A workspace that has no room for the partial sums of every split (the
+    sizes are the plans with one split per 1024 points) is accepted, and the
+    data are those of the full plan up to the order of the sums (n eps)."""
+    import ctypes as C
+    from paper_2604_15796_amd import fwi as F
+    p = W.small2d(seed=5, nx=nx, nz=nz, ne=ne, nf=nf)
+    o = F.SolveOptions(precision=F.FWI_FP32_REFINE, rtol=1e-8, restart=8, max_rhs=64)
+    prob, co = F.ProblemArgs(p), o.c()
+    full = C.c_size_t()
+    assert ctx.L.fwi_workspace_size(prob.ref(), C.byref(co), 0, C.byref(full)) == 0 and full.value > nbytes
+    cc = torch.as_tensor(np.ascontiguousarray(p.c)).to(torch.float64).to(DEV).reshape(-1)
+    out = []
+    for size in (full.value, nbytes):
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        d = torch.empty((nf, ne, ne), dtype=torch.complex128, device=DEV)
+        assert ctx.L.fwi_set_workspace(ctx.h, C.c_void_p(ws.data_ptr()), size) == 0
+        rc = ctx.L.fwi_forward(ctx.h, prob.ref(), C.c_void_p(cc.data_ptr()), None, C.byref(co),
+                               C.c_void_p(d.data_ptr()), None, None)
+        torch.cuda.synchronize()
+        ctx.L.fwi_set_workspace(ctx.h, None, 0)
+        assert rc == 0
+        out.append(d.cpu().numpy())
+    assert _err(out[1], out[0]) < 1e-12
