@@ -2383,12 +2383,22 @@ int fwi_green_spectrum(fwi_ctx* c, const fwi_problem* p, int l, void* out) {
       return FWI_OK;
     }
     // the operator's spectra have other lengths: this one on the ABI's grid
+    // (in the workspace; a caller's that is too small is left alone, since the
+    // call needs none on other grids)
+    Arena dry, a;
+    dry.take<c128>(2 * np);
     c128* table = nullptr;
-    FWI_HIP(hipMalloc((void**)&table, sizeof(c128) * 2 * np));
+    const bool own = c->ws_ext && dry.used > c->ws_ext_bytes;
+    if (own) {
+      FWI_HIP(hipMalloc((void**)&table, sizeof(c128) * 2 * np));
+    } else {
+      bind_workspace(c, a, dry.used);
+      table = a.take<c128>(2 * np);
+    }
     launch_green_table(pub, c->pc.k[l], table, c->stream);
     launch_fft_full(pub, c->tw, table, table + np, (c128*)out, c->stream);
     const hipError_t e = hipStreamSynchronize(c->stream);
-    FWI_HIP(hipFree(table));
+    if (own) FWI_HIP(hipFree(table));
     FWI_HIP(e);
     return FWI_OK;
   });
