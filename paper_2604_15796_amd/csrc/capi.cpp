@@ -743,7 +743,11 @@ struct ArnoldiDriver {
   // 2048 points per vector and the launch is short (plane waves 192x160, 3360
   // workgroups: 1.2% of the gradient; 256^2, 512 right-hand sides: the launch is
   // 5 us of 800 per step, less than the workgroups' sums).
-  bool fuse_hsum(int parts) const { return !g.xy && parts <= 64 && (long)parts * ks.B <= 4096; }
+  // Only with the built-in row tile: the larger ones have no registers to spare.
+  bool fuse_hsum(int parts) const {
+    return !g.xy && parts <= 64 && (long)parts * ks.B <= 4096 &&
+           tune_variant(PK_ROW_FWD, std::is_same<T, double>::value, g.Lx) == 0;
+  }
   // orthogonalise w_{j+1} (and transform it unless this was the last step),
   // then the rotations of column j
   void orth_givens(int j, bool transform) {

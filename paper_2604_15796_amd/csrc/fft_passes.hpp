@@ -78,7 +78,19 @@ constexpr int kMaxDotVec = 33;  // basis vectors of the largest restart (32) + 1
 // ------------------------------------------------------------- row pass 1 ---
 // Input of the first pass: the rows of x as they are, or a combination with
 // basis vectors formed first (see k_row_fwd).
-enum RowInKind { RI_PLAIN = 0, RI_UPD32 = 1, RI_UPD64 = 2, RI_ORTH = 3, RI_ORTH_ONLY = 4, RI_START = 5 };
+enum RowInKind {
+  RI_PLAIN = 0,
+  RI_UPD32 = 1,
+  RI_UPD64 = 2,
+  RI_ORTH = 3,
+  RI_ORTH_ONLY = 4,
+  RI_START = 5,
+  RI_ORTH_SUM = 6,       // RI_ORTH and RI_ORTH_ONLY that sum the inner-product
+  RI_ORTH_ONLY_SUM = 7,  // parts themselves
+};
+__host__ __device__ constexpr bool row_in_sums(int k) { return k == RI_ORTH_SUM || k == RI_ORTH_ONLY_SUM; }
+__host__ __device__ constexpr bool row_in_orth_only(int k) { return k == RI_ORTH_ONLY || k == RI_ORTH_ONLY_SUM; }
+__host__ __device__ constexpr bool row_in_orth(int k) { return k == RI_ORTH || row_in_orth_only(k) || row_in_sums(k); }
 
 template <typename T>
 struct RowFwdArgs {
@@ -101,8 +113,8 @@ struct RowFwdArgs {
   cplx<T>* lc_out;       // = x, written
   double* lc_rowpart;    // orthogonalisation / start: |v|^2 per row
   const c128* lc_src;    // start: the right-hand sides
-  int per_rhs;           // workgroups per RHS (0: rows packed across RHS)
   // orthogonalisation with the sum of the inner-product parts (see OrthIn)
+  int per_rhs;           // workgroups per RHS
   int ndot, nB;
   const c128* dotp;
   const cplx<T>* vscale;
@@ -123,12 +135,17 @@ using lc_basis_t = std::conditional_t<K == RI_UPD32, float, std::conditional_t<K
 //     the vector's scale, accumulated in T like every vector update of the
 //     solver), stored, and |v|^2 summed per row in FP64 into rowpart;
 //     RI_ORTH_ONLY stops there (no transform);
+//   RI_ORTH_SUM / RI_ORTH_ONLY_SUM: the same with the coefficients summed from
+//     their parts first, a workgroup's rows all of one RHS. Kinds of their own:
+//     the coefficient's place chosen at run time inside the basis loop keeps
+//     fewer loads in flight (complex64 pass at 256^2 / 384^2 / 512^2, full
+//     batches: 275 / 544 / 611 us against 271 / 537 / 605);
 //   RI_START (first cycle, x_0 = 0): x = src rounded to T (src complex128),
 //     with |src|^2 summed per row in FP64 into rowpart.
 template <typename T, int L, int NLV, bool HIN, int K = RI_PLAIN>
 __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
   using C = LineCfg<T, L, NLV, NT, false>;
-  constexpr bool ORTH = K == RI_ORTH || K == RI_ORTH_ONLY;
+  constexpr bool ORTH = row_in_orth(K), SUM = row_in_sums(K);
   constexpr bool START = K == RI_START;
   constexpr bool NORM = ORTH || START;  // per-row sums of |v|^2
   __shared__ cplx<T> sh[C::LDS_ELEMS];
@@ -137,9 +154,9 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
   __shared__ int s_ok[C::NL];
   __shared__ int s_k[K != RI_PLAIN ? C::NL : 1];
   __shared__ int s_b[K != RI_PLAIN ? C::NL : 1];
-  __shared__ c128 s_coef[ORTH ? kMaxDotVec : 1];
+  __shared__ c128 s_coef[SUM ? kMaxDotVec : 1];
   long g0 = (long)blockIdx.x * C::NL, gend = a.nrows;  // the workgroup's first row, end of its rows
-  if (ORTH && a.per_rhs) {
+  if constexpr (SUM) {
     const unsigned b = blockIdx.x / (unsigned)a.per_rhs, part = blockIdx.x % (unsigned)a.per_rhs;
     g0 = (long)b * a.rows_per_rhs + (long)part * C::NL;
     gend = (long)(b + 1) * a.rows_per_rhs;
@@ -185,29 +202,27 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
     static_assert(ORTH || START || sizeof(T) == 8, "the solution update is complex128");
     using TB = lc_basis_t<T, K>;
     using TA = std::conditional_t<ORTH, T, double>;  // accumulation type
-    if constexpr (ORTH) {
-      if (a.ndot) {
-        // column of H and the coefficients from the parts (one RHS): wave w
-        // sums vectors w, w + 4, ..., each lane a fixed subset of the parts
-        const int lane = threadIdx.x & 63, b = s_b[0];
-        for (int i = threadIdx.x >> 6; i < a.lc_nvec; i += NT / 64) {
-          double r = 0.0, m = 0.0;
-          for (int k = lane; k < a.ndot; k += 64) {
-            const c128 d = a.dotp[((long)b * a.ndot + k) * a.lc_cstride + i];
-            r += d.x;
-            m += d.y;
-          }
-          r = wave_sum(r);
-          m = wave_sum(m);
-          if (lane == 0) {
-            const double sc = (double)a.vscale[(long)i * a.nB + b].x;
-            s_coef[i] = mk(-(r * sc), -(m * sc));
-            if (g0 == (long)b * a.rows_per_rhs)
-              a.H[((long)b * a.lc_cstride + i) * (a.lc_cstride - 1) + a.lc_nvec - 1] = mk(r, m);
-          }
+    if constexpr (SUM) {
+      // column of H and the coefficients from the parts (one RHS): wave w
+      // sums vectors w, w + 4, ..., each lane a fixed subset of the parts
+      const int lane = threadIdx.x & 63, b = s_b[0];
+      for (int i = threadIdx.x >> 6; i < a.lc_nvec; i += NT / 64) {
+        double r = 0.0, m = 0.0;
+        for (int k = lane; k < a.ndot; k += 64) {
+          const c128 d = a.dotp[((long)b * a.ndot + k) * a.lc_cstride + i];
+          r += d.x;
+          m += d.y;
         }
-        __syncthreads();
+        r = wave_sum(r);
+        m = wave_sum(m);
+        if (lane == 0) {
+          const double sc = (double)a.vscale[(long)i * a.nB + b].x;
+          s_coef[i] = mk(-(r * sc), -(m * sc));
+          if (g0 == (long)b * a.rows_per_rhs)
+            a.H[((long)b * a.lc_cstride + i) * (a.lc_cstride - 1) + a.lc_nvec - 1] = mk(r, m);
+        }
       }
+      __syncthreads();
     }
     // the points the first stage will ask this thread for: slot t, leg r
     constexpr int R0 = stage_radix(L, 0, 0, C::BIG);
@@ -248,7 +263,7 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
         C::template split<R0>(t, line, j);
         if (line >= C::NL) line = C::NL - 1;
         const bool use = ORTH || i < s_k[line];  // every RHS of an orthogonalisation has nvec vectors
-        const c128 c64 = ORTH && a.ndot ? s_coef[i] : a.lc_coef[(long)s_b[line] * a.lc_cstride + i];
+        const c128 c64 = SUM ? s_coef[i] : a.lc_coef[(long)s_b[line] * a.lc_cstride + i];
         const cplx<TA> c = mk((TA)c64.x, (TA)c64.y);
 #pragma unroll
         for (int r = 0; r < RIN0; ++r) {
@@ -283,7 +298,7 @@ __global__ void __launch_bounds__(NT) k_row_fwd(RowFwdArgs<T> a) {
         }
       }
     }
-    if constexpr (K != RI_ORTH_ONLY) {
+    if constexpr (!row_in_orth_only(K)) {
       auto src = [&](int line, int pb, int ro, int t, int r) -> cplx<T> {
         const int p = pb + ro;
         const int pc = p < a.nin ? p : a.nin - 1;
@@ -640,18 +655,25 @@ __global__ void __launch_bounds__(NTV) k_strided(StridedArgs<T> a) {
 
 // ---------------------------------------------------------------- dispatch ---
 template <typename T, int L, int V>
-void launch_row_fwd_v(const RowFwdArgs<T>& args, hipStream_t st) {
+void launch_row_fwd_v(const RowFwdArgs<T>& a, hipStream_t st) {
   constexpr int NL = row_nl<T, L, V>();
-  RowFwdArgs<T> a = args;
-  unsigned grid = (unsigned)((a.nrows + NL - 1) / NL);
+  const unsigned grid = (unsigned)((a.nrows + NL - 1) / NL);
   if (grid == 0) return;
-  if (a.ndot) {  // the coefficients are formed per workgroup: one RHS each
-    a.per_rhs = (a.rows_per_rhs + NL - 1) / NL;
-    grid = (unsigned)(a.nrows / a.rows_per_rhs) * (unsigned)a.per_rhs;
-  }
   if (a.kind != RI_PLAIN) {
     if (2 * a.nin > L) throw Error(-6, "combined row inputs need zero-padded rows");
-    if (a.kind == RI_ORTH) {
+    if (row_in_sums(a.kind)) {
+      // the built-in tile only, as the caller decided; the coefficients are formed
+      // per workgroup, so each takes rows of one RHS
+      if constexpr (V == 0) {
+        RowFwdArgs<T> b = a;
+        b.per_rhs = (a.rows_per_rhs + NL - 1) / NL;
+        const unsigned wg = (unsigned)(a.nrows / a.rows_per_rhs) * (unsigned)b.per_rhs;
+        if (a.kind == RI_ORTH_SUM) FWI_TIMED_LAUNCH((k_row_fwd<T, L, NL, true, RI_ORTH_SUM>), dim3(wg), dim3(NT), 0, st, b);
+        else FWI_TIMED_LAUNCH((k_row_fwd<T, L, NL, true, RI_ORTH_ONLY_SUM>), dim3(wg), dim3(NT), 0, st, b);
+      } else {
+        throw Error(-6, "the fused coefficient sum takes the built-in row tile");
+      }
+    } else if (a.kind == RI_ORTH) {
       FWI_TIMED_LAUNCH((k_row_fwd<T, L, NL, true, RI_ORTH>), dim3(grid), dim3(NT), 0, st, a);
     } else if (a.kind == RI_ORTH_ONLY) {
       FWI_TIMED_LAUNCH((k_row_fwd<T, L, NL, true, RI_ORTH_ONLY>), dim3(grid), dim3(NT), 0, st, a);
@@ -926,6 +948,7 @@ void launch_vie_rows(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
     f.lc_rowpart = orth->rowpart;
     if (orth->ndot) {
       if (orth->nvec > kMaxDotVec) throw Error(-6, "too many vectors for the fused coefficient sum");
+      f.kind = orth->transform ? RI_ORTH_SUM : RI_ORTH_ONLY_SUM;
       f.ndot = orth->ndot;
       f.nB = B;
       f.dotp = orth->dotp;
@@ -947,7 +970,7 @@ void launch_vie_rows(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
   const int cls = orth ? (orth->transform ? KC_ORTH_FWD : KC_ORTH) : KC_ROW_FWD;
   if constexpr (sizeof(T) == 4) {
     if (g.xy && f.ndot) throw Error(-6, "the fused lateral-elevation pass takes the coefficients");
-    if (g.xy && f.kind != RI_ORTH_ONLY) {
+    if (g.xy && !row_in_orth_only(f.kind)) {
       // fused lateral-elevation pass: the operand straight to the padded
       // spectrum U2 (class-major), no x-pass intermediate
       if (!U2) throw Error(-6, "the fused lateral-elevation pass needs the y-pass buffer");
