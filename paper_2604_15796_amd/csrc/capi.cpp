@@ -526,20 +526,14 @@ double build_cache(fwi_ctx* c, const fwi_problem* p, ProblemCache& pc, const std
   }
   std::memcpy(&small[off_elem], p->elem_xyz, sizeof(double) * 3 * pc.ne);
   FWI_HIP(hipMemcpyAsync(pc.k2, small.data(), small.size(), hipMemcpyHostToDevice, st));
-  // the circulant table and the FFT's work grid lie in the incident fields'
-  // buffer, which is filled after the spectra (few elements: in their own)
-  c128 *table = pc.P0, *own = nullptr;
-  if (sizeof(c128) * 2 * np > need[2]) {
-    FWI_HIP(hipMalloc((void**)&own, sizeof(c128) * 2 * np));
-    table = own;
-  }
   Aperture ap{};
   ap.hw = 0.5 * p->elem_width;
   ap.hh = 0.5 * p->elem_height;
   ap.rule = gauss_legendre(ap.hw > 0.0 || ap.hh > 0.0 ? p->elem_quad : 1);
   for (int l = 0; l < pc.nf; ++l) {
-    launch_green_table(g, pc.k[l], table, st);
-    launch_fft_full(g, c->tw, table, table + np, pc.ghat64 + (long)l * np, st);
+    // the circulant table at the spectrum's place, transformed there
+    launch_green_table(g, pc.k[l], pc.ghat64 + (long)l * np, st);
+    launch_fft_full(g, c->tw, pc.ghat64 + (long)l * np, st);
   }
   if (g.xy) {
     for (int l = 0; l < pc.nf; ++l)
@@ -550,7 +544,6 @@ double build_cache(fwi_ctx* c, const fwi_problem* p, ProblemCache& pc, const std
   for (int l = 0; l < pc.nf; ++l)
     launch_incident(g, pc.k[l], pc.ne, pc.elems, ap, pc.P0 + (long)l * pc.ne * n, st);
   FWI_HIP(hipStreamSynchronize(st));
-  if (own) FWI_HIP(hipFree(own));
   pc.key = key;
   return now_ms() - t0;
 }
@@ -2383,27 +2376,13 @@ int fwi_green_spectrum(fwi_ctx* c, const fwi_problem* p, int l, void* out) {
     const long np = pub.npad();
     if (pub.Lx == c->pc.g.Lx && pub.Ly == c->pc.g.Ly && pub.Lz == c->pc.g.Lz) {
       launch_copy_c128(np, c->pc.ghat64 + (long)l * np, (c128*)out, c->stream);
-      FWI_HIP(hipStreamSynchronize(c->stream));
-      return FWI_OK;
-    }
-    // the operator's spectra have other lengths: this one on the ABI's grid
-    // (in the workspace; a caller's that is too small is left alone, since the
-    // call needs none on other grids)
-    Arena dry, a;
-    dry.take<c128>(2 * np);
-    c128* table = nullptr;
-    const bool own = c->ws_ext && dry.used > c->ws_ext_bytes;
-    if (own) {
-      FWI_HIP(hipMalloc((void**)&table, sizeof(c128) * 2 * np));
     } else {
-      bind_workspace(c, a, dry.used);
-      table = a.take<c128>(2 * np);
+      // the operator's spectra have other lengths: this one on the ABI's grid,
+      // formed where it goes (like the copy, the call needs no memory)
+      launch_green_table(pub, c->pc.k[l], (c128*)out, c->stream);
+      launch_fft_full(pub, c->tw, (c128*)out, c->stream);
     }
-    launch_green_table(pub, c->pc.k[l], table, c->stream);
-    launch_fft_full(pub, c->tw, table, table + np, (c128*)out, c->stream);
-    const hipError_t e = hipStreamSynchronize(c->stream);
-    if (own) FWI_HIP(hipFree(table));
-    FWI_HIP(e);
+    FWI_HIP(hipStreamSynchronize(c->stream));
     return FWI_OK;
   });
 }

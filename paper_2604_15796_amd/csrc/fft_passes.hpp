@@ -1183,11 +1183,11 @@ void launch_vie(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, const
 }
 
 #ifdef FWI_FFT_WITH_FULL
-void launch_fft_full(const Geo& g, const Twiddles& tw, const c128* in, c128* work, c128* out, hipStream_t st) {
-  // rows: in -> work (full length, no padding)
+void launch_fft_full(const Geo& g, const Twiddles& tw, c128* u, hipStream_t st) {
+  // every pass in place: a workgroup reads all its lines before it stores any
   RowFwdArgs<double> f{};
-  f.x = in;
-  f.out = (g.dim == 2) ? out : work;
+  f.x = u;
+  f.out = u;
   f.tw = tw.get<double>(g.Lx);
   f.nrows = (long)g.Lz * g.Ly;
   f.rows_per_rhs = (int)f.nrows;
@@ -1196,8 +1196,8 @@ void launch_fft_full(const Geo& g, const Twiddles& tw, const c128* in, c128* wor
   row_fwd_call<double>(g.Lx, f, st);
   if (g.dim == 3) {
     StridedArgs<double> s{};
-    s.in = work;
-    s.out = out;
+    s.in = u;
+    s.out = u;
     s.tw = tw.get<double>(g.Ly);
     s.in_ps = s.out_ps = (long)g.Ly * g.Lx;
     s.pstride = g.Lx;
@@ -1207,8 +1207,8 @@ void launch_fft_full(const Geo& g, const Twiddles& tw, const c128* in, c128* wor
     strided_call<double>(g.Ly, s, g.Lz, 0, st);
   }
   StridedArgs<double> z{};
-  z.in = out;
-  z.out = out;
+  z.in = u;
+  z.out = u;
   z.tw = tw.get<double>(g.Lz);
   z.in_ps = z.out_ps = 0;
   z.pstride = (long)g.Ly * g.Lx;

@@ -239,9 +239,9 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
                      cplx<T>* y, const cplx<T>* rhs, int epi, hipStream_t st, c64* y32 = nullptr,
                      double* rowpart = nullptr, VieDots* dots = nullptr);
 
-// Forward FFT of a full padded grid [Lz][Ly][Lx] (no padding, no crop), in place
-// through `work` of the same size: out = FFT(in). Used for the Green spectrum.
-void launch_fft_full(const Geo& g, const Twiddles& tw, const c128* in, c128* work, c128* out, hipStream_t st);
+// Forward FFT of a full padded grid u [Lz][Ly][Lx] (no padding, no crop), in
+// place. Used for the Green spectrum.
+void launch_fft_full(const Geo& g, const Twiddles& tw, c128* u, hipStream_t st);
 
 // Zero-padded forward FFT of [nz][ny][nx] data into [Lz][Ly][Lx] (diagnostics).
 template <typename T>

@@ -25,4 +25,6 @@ void violation(const char* what);
 extern int iters_base, iters_spread;
 // Free device memory reported by hipMemGetInfo.
 extern size_t mem_free;
+// hipMalloc calls so far; the calls that may still succeed (negative: all).
+extern long malloc_calls, malloc_left;
 }  // namespace emu

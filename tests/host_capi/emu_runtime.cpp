@@ -60,6 +60,7 @@ struct EmuEvent {
 namespace emu {
 int iters_base = 12, iters_spread = 5;
 size_t mem_free = size_t(8) << 30;
+long malloc_calls = 0, malloc_left = -1;
 static Counts g_counts;
 Counts& counts() { return g_counts; }
 void violation(const char* what) {
@@ -153,7 +154,9 @@ hipError_t hipMemGetInfo(size_t* free_b, size_t* total_b) {
 }
 hipError_t hipMalloc(void** p, size_t bytes) {
   if (hipError_t e = prohibited("hipMalloc while capturing")) return e;
-  *p = std::malloc(bytes ? bytes : 1);
+  emu::malloc_calls += 1;
+  *p = emu::malloc_left == 0 ? nullptr : std::malloc(bytes ? bytes : 1);
+  if (emu::malloc_left > 0) emu::malloc_left -= 1;
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 hipError_t hipFree(void* p) {

@@ -1,0 +1,79 @@
+// Single calls of the C ABI on the host stand-in (see driver.cpp), each a
+// condition that the call sequences there do not set up. Prints "ok <name>" per
+// check; run under the sanitizers.
+#include <complex>
+#include <cstdio>
+#include <cstdlib>
+#include <string>
+#include <vector>
+
+#include "emu.hpp"
+#include "fwi.h"
+
+namespace {
+
+using cd = std::complex<double>;
+int g_fail = 0;
+void expect(bool ok, const char* what) {
+  std::printf("%s %s\n", ok ? "ok" : "FAILED", what);
+  if (!ok) g_fail = 1;
+}
+
+struct Prob {
+  fwi_problem p{};
+  std::vector<double> f, e;
+  long n = 0, npad = 0;
+  Prob(int nx, int ny, int nz, int ne, int nf) {
+    p.dim = ny > 1 ? 3 : 2;
+    p.nx = nx;
+    p.ny = ny;
+    p.nz = nz;
+    p.dx = 0.154e-3;
+    p.c0 = 1540.0;
+    p.nf = nf;
+    p.ne = ne;
+    for (int l = 0; l < nf; ++l) f.push_back(0.3e6 + 0.1e6 * l);
+    for (int k = 0; k < ne; ++k) {
+      e.push_back((k + 0.5) / ne * nx * p.dx);
+      e.push_back(p.dim == 3 ? ny * p.dx / 2 : 0.0);
+      e.push_back(0.0);
+    }
+    p.freq_hz = f.data();
+    p.elem_xyz = e.data();
+    n = (long)nx * ny * nz;
+    npad = (long)fwi_padded_length(nx) * (ny > 1 ? fwi_padded_length(ny) : 1) * fwi_padded_length(nz);
+  }
+};
+
+// The spectrum call takes no memory on any grid, also where the operator pads
+// to other lengths than the call's, and leaves a caller's workspace alone.
+void spectrum(fwi_ctx* ctx) {
+  for (int k = 0; k < 4; ++k) {
+    Prob q = k == 0 ? Prob(37, 1, 70, 3, 2) : k == 1 ? Prob(40, 36, 30, 2, 1) : k == 2 ? Prob(64, 1, 64, 2, 1) : Prob(33, 20, 40, 2, 1);
+    std::vector<cd> p0((size_t)q.p.ne * q.n), out((size_t)q.npad);
+    bool ok = fwi_incident(ctx, &q.p, 0, p0.data()) == FWI_OK;  // the problem's cache
+    std::vector<char> ws(256, 7);
+    for (int own = 0; own < 2; ++own) {
+      if (own) fwi_set_workspace(ctx, ws.data(), ws.size());
+      emu::malloc_left = 0;
+      const long before = emu::malloc_calls;
+      ok = ok && fwi_green_spectrum(ctx, &q.p, q.p.nf - 1, out.data()) == FWI_OK && emu::malloc_calls == before;
+      emu::malloc_left = -1;
+      fwi_set_workspace(ctx, nullptr, 0);
+    }
+    for (char v : ws) ok = ok && v == 7;
+    expect(ok, "spectrum without memory");
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  fwi_ctx* ctx = nullptr;
+  if (fwi_create(&ctx, 0, nullptr) != FWI_OK) return 1;
+  if (what == "spectrum") spectrum(ctx);
+  fwi_destroy(ctx);
+  if (emu::counts().violations) g_fail = 1;
+  return g_fail;
+}

@@ -337,13 +337,12 @@ void launch_vie(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, const
   launch_vie_tail<T>(g, tw, B, x, scale, active, ghat, rhs_freq, U1, U2, y, rhs, epi, st, y32, rowpart, dots);
 }
 
-void launch_fft_full(const Geo& g, const Twiddles& tw, const c128* in, c128* work, c128* out, hipStream_t st) {
+void launch_fft_full(const Geo& g, const Twiddles& tw, c128* u, hipStream_t st) {
   (void)tw.get<double>(g.Lx);
   const long np = g.npad();
   emu::submit(st, "fft_full", [=] {
-    rd(in, 16 * np);
-    wr(work, 16 * np);
-    wr(out, 16 * np);
+    rd(u, 16 * np);
+    wr(u, 16 * np);
   });
 }
 
