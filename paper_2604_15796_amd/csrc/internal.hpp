@@ -248,6 +248,15 @@ template <typename T>
 void launch_fft_padded(const Geo& g, const Twiddles& tw, const cplx<T>* in, cplx<T>* U1, cplx<T>* out,
                        hipStream_t st);
 
+// A launch holds fewer than 2^32 work items, so an element-wise launch over a
+// count without a smaller bound (the spectra of all frequencies reach 2^32
+// values at 512^3 with four) runs in pieces: f(first, count) per piece.
+constexpr long kLaunchItems = 1L << 30;
+template <typename F>
+void in_launches(long count, F&& f) {
+  for (long o = 0; o < count; o += kLaunchItems) f(o, count - o < kLaunchItems ? count - o : kLaunchItems);
+}
+
 // ---------------------------------------------------------- setup kernels ---
 // kappa_0 rho_0 of the background: 1/c0^2 - alpha0^2/(4 pi^2) + i alpha0/(pi c0)
 inline c128 kappa0_rho(double c0, double alpha0) {

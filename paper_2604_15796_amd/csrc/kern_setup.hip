@@ -287,9 +287,10 @@ __global__ void k_cast_64_32(long count, const c128* __restrict__ in, c64* __res
   if (i < count) out[i] = cvt<float>(in[i]);
 }
 void launch_cast_64_32(long count, const c128* in, c64* out, hipStream_t st) {
-  if (count == 0) return;
-  hipLaunchKernelGGL(k_cast_64_32, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, count, in, out);
-  FWI_LAUNCH_CHECK();
+  in_launches(count, [&](long o, long c) {
+    hipLaunchKernelGGL(k_cast_64_32, dim3((unsigned)((c + 255) / 256)), dim3(256), 0, st, c, in + o, out + o);
+    FWI_LAUNCH_CHECK();
+  });
 }
 
 // The complex64 kernel spectrum of a geometry with fused lateral-elevation

@@ -9,6 +9,7 @@
 
 #include "emu.hpp"
 #include "fwi.h"
+#include "internal.hpp"
 
 namespace {
 
@@ -66,6 +67,20 @@ void spectrum(fwi_ctx* ctx) {
   }
 }
 
+// Element-wise launches over any count: contiguous pieces, each well below the
+// 2^32 work items that a launch holds.
+void launches(fwi_ctx*) {
+  for (long count : {0L, 1L, 1L << 30, (1L << 30) + 1, 1L << 32, (5L << 32) + 3}) {
+    long next = 0;
+    bool ok = true;
+    fwi::in_launches(count, [&](long o, long c) {
+      ok = ok && o == next && c > 0 && (c + 255) / 256 * 256 < (1L << 32);
+      next = o + c;
+    });
+    expect(ok && next == count, "launch pieces");
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -73,6 +88,7 @@ int main(int argc, char** argv) {
   fwi_ctx* ctx = nullptr;
   if (fwi_create(&ctx, 0, nullptr) != FWI_OK) return 1;
   if (what == "spectrum") spectrum(ctx);
+  if (what == "launches") launches(ctx);
   fwi_destroy(ctx);
   if (emu::counts().violations) g_fail = 1;
   return g_fail;
