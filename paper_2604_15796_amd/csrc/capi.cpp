@@ -38,21 +38,52 @@ thread_local int tl_force_variant = -1;
 thread_local int tl_force_wide = 0;
 thread_local int tl_xy_off = 0;
 
-// Built-in tiles, from timings of every variant on an MI355X (us per launch;
-// batches that fill the device):
-//  * convolution, complex128: (8, 256) against (16, 256): L 64 40 / 31, 96 139 /
-//    126, 128 233 / 212, 192 1855 / 1466, equal elsewhere (the column counts
-//    coincide from 512 on); 512: (8, 512 threads) 549 against 592 (twice the
-//    waves in flight).
-//  * convolution, complex64: (16, 512) is the fastest from 128 on except 192
-//    (the radix 16 x 12 plan needs 12 points per thread); L 48, 64, 96:
-//    (16, 256) 10.5, 19, 46 against 12.5, 25, 57.
-//  * elevation passes: complex128 from 128 on (16, 512): 256 845 against 925.
-int default_variant(int pass, bool dbl, int L) {
+// Built-in tiles, from timings of every variant on an MI355X (us per launch).
+// Complex128 strided passes have a wide tile (16 columns; elevation 512 threads)
+// and a narrow one (8 columns, 256 threads: twice the workgroups). The wide tile
+// is the faster one once the data no longer stay in the 256 MB last-level cache
+// between the passes, the narrow one before that:
+//  * convolution, narrow / wide: L 128, 2D 64^2, 512, 1024 and 2048 planes 26.0 /
+//    26.9, 45.7 / 46.4, 144 / 115; 3D 64^3, 4 and 8 volumes 26.6 / 28.4, 90 / 74;
+//    L 256, 2D 128^2, 128, 256 and 512 planes 28.6 / 29.6, 50.2 / 52.1, 125 / 118;
+//    L 96 the same within 3% on both sides.
+//  * elevation, both passes: L 256, 128 x 128 x 96, 1, 2 and 4 volumes 42.2 / 44.4,
+//    94.2 / 90.6, 229 / 215; L 192 at 96 x 96 x 72, 2 and 4 volumes 37.1 / 37.8,
+//    72.6 / 70.5; L 128 at 64 x 64 x 48, 8 and 16 volumes 41.1 / 42.0, 86 / 80.
+//  * Short lines are bound by the workgroups' latency instead: L 64, 2D 32^2, 64,
+//    128 and 256 planes 5.65 / 6.00, 6.63 / 6.92, 9.85 / 9.06 (L 48: 768 workgroups
+//    6.91 / 7.24, 1536 11.4 / 11.1); with few planes to share a spectrum tile the
+//    narrow one holds on longer (32^3, 4, 6 and 8 volumes 8.2 / 9.5, 12.0 / 13.9,
+//    13.1 / 11.9).
+//  * L 192 (the radix 16 x 12 plan needs the wide tile): 128 workgroups 8.23 / 8.50,
+//    256 10.2 / 9.9, large batches 1855 / 1466.
+//  * Other lengths take one tile at every size: convolution 512 (8, 512 threads)
+//    against (8, 256) 8.9 / 9.7 to 549 / 592; elevation below 128 and at 1024 (8, 256)
+//    (1024: 63.3 against 66.3), else (16, 512).
+// Complex64 convolution: (16, 512) is the fastest from 128 on except 192 (radix 16 x
+// 12 needs 12 points per thread); L 48, 64, 96: (16, 256) 10.5, 19, 46 against 12.5,
+// 25, 57 on full batches, the same within 2% on short ones. Elevation: (16, 256).
+constexpr double kConvCached = 220e6, kElevationCached = 280e6;
+int default_variant(int pass, bool dbl, int L, const LaunchSize& sz) {
   if (pass == PK_ROW_FWD || pass == PK_ROW_INV) return 0;  // 2048 points per workgroup
-  if (pass == PK_CONV && dbl) return L == 512 ? 2 : 1;
+  if (pass == PK_CONV && dbl) {
+    if (L == 512) return 2;
+    if (L == 192) return sz.tiles < 256 ? 0 : 1;
+    if (L <= 64 && sz.planes >= 8) return sz.tiles < 800 ? 0 : 1;
+    return sz.bytes < kConvCached ? 0 : 1;
+  }
   if (pass == PK_CONV) return L == 48 || L == 64 || L == 96 || L == 192 ? 1 : 2;
-  return dbl ? (L >= 128 ? 2 : 0) : 1;
+  if (!dbl) return 1;
+  if (L < 128 || L == 1024) return 0;
+  return L <= 256 && sz.bytes < kElevationCached ? 0 : 2;
+}
+LaunchSize strided_size(const Geo& g, int B, int pass, size_t es) {
+  LaunchSize s;
+  const long lines = pass == PK_CONV && g.dim == 3 ? (long)g.Ly * g.Lx : g.Lx;
+  s.planes = pass == PK_CONV ? B : (long)B * g.nz;
+  s.tiles = (lines + 15) / 16 * s.planes;
+  s.bytes = (double)es * B * (double)(g.n() + g.u1() + (g.dim == 3 ? g.u2() : 0));
+  return s;
 }
 
 // Fastest variant by measured time; another variant replaces the default only
@@ -64,14 +95,14 @@ int pick_variant(const double* t, int dflt) {
   return best;
 }
 
-int tune_variant(int pass, bool dbl, int L) {
+int tune_variant(int pass, bool dbl, int L, const LaunchSize& sz) {
   if (tl_force_variant >= 0) return tl_force_variant;
   const int li = length_index(L);
   if (tl_tune && li >= 0) {
     const int v = tl_tune->v[pass][dbl ? 1 : 0][li];
     if (v >= 0 && v < kNumVariants) return v;
   }
-  return default_variant(pass, dbl, L);
+  return default_variant(pass, dbl, L, sz);
 }
 
 int length_index(int L) {
@@ -2600,27 +2631,31 @@ int fwi_autotune(fwi_ctx* c, const fwi_problem* p, int precision, int B, int rep
     tl_prof = saved;
     tl_force_variant = -1;
     // class -> pass kind and length
+    // (the comparison is with the built-in tile of this launch)
     const int kinds[KC_COUNT] = {PK_ROW_FWD, PK_CONV, PK_ROW_INV, PK_STRIDED, PK_STRIDED, -1, -1, -1};
     const int lens[KC_COUNT] = {g.Lx, g.Lz, g.Lx, g.Ly, g.Ly, 0, 0, 0};
     double strided_sum[kNumVariants] = {};
     for (int v = 0; v < kNumVariants; ++v) strided_sum[v] = t[KC_Y_FWD][v] + t[KC_Y_INV][v];
+    auto built_in = [&](int k) {
+      return default_variant(kinds[k], dbl, lens[k], strided_size(g, B, kinds[k], es));
+    };
     for (int k = 0; k < KC_COUNT; ++k) {
       if (kinds[k] < 0 || k == KC_Y_INV) continue;
       const double* tv = k == KC_Y_FWD ? strided_sum : t[k];
       if (tv[0] == 0.0 || length_index(lens[k]) < 0) continue;  // one tile only
-      c->tune.v[kinds[k]][dbl ? 1 : 0][length_index(lens[k])] =
-          (signed char)pick_variant(tv, default_variant(kinds[k], dbl, lens[k]));
+      c->tune.v[kinds[k]][dbl ? 1 : 0][length_index(lens[k])] = (signed char)pick_variant(tv, built_in(k));
     }
     if (rep) {
       for (int k = 0; k < 5; ++k) {
         for (int v = 0; v < kNumVariants; ++v) rep->variant_ms[k][v] = t[k][v];
-        rep->default_variant[k] = kinds[k] >= 0 ? default_variant(kinds[k], dbl, lens[k]) : -1;
-        rep->variant[k] = t[k][0] > 0.0 ? pick_variant(t[k], rep->default_variant[k] >= 0 ? rep->default_variant[k] : 0)
-                                         : -1;
+        // the elevation passes are tuned on their summed time; lengths with
+        // one tile report the built-in number
+        const double* tv = k == KC_Y_FWD || k == KC_Y_INV ? strided_sum : t[k];
+        rep->default_variant[k] = built_in(k);
+        rep->variant[k] = t[k][0] == 0.0                ? -1
+                          : length_index(lens[k]) < 0 ? rep->default_variant[k]
+                                                      : pick_variant(tv, rep->default_variant[k]);
       }
-      // the elevation passes are tuned on their summed time
-      if (strided_sum[0] > 0.0) rep->variant[KC_Y_FWD] = rep->variant[KC_Y_INV] =
-          pick_variant(strided_sum, default_variant(PK_STRIDED, dbl, g.Ly));
     }
     return FWI_OK;
   });

@@ -825,8 +825,10 @@ constexpr int op_strided_variant(int L) {
   return sizeof(T) == 4 ? 1 : L >= 128 ? 2 : 0;
 }
 
+// sz: the launch within the operator; without one (spectra, diagnostics) the
+// pass's own input and output
 template <typename T>
-void strided_call(int L, const StridedArgs<T>& a, long planes, int mode, hipStream_t st) {
+void strided_call(int L, const StridedArgs<T>& a, long planes, int mode, hipStream_t st, const LaunchSize* sz = nullptr) {
 #define FWI_X(LL)                                                                              \
   case LL:                                                                                     \
     if (mode == 2) launch_strided_v<T, LL, op_conv_variant<T>(LL), 1>(a, planes, mode, st);    \
@@ -834,10 +836,13 @@ void strided_call(int L, const StridedArgs<T>& a, long planes, int mode, hipStre
     return;
   switch (L) { FWI_OP_LENGTHS(FWI_X) }
 #undef FWI_X
-  int v = tune_variant(mode == 2 ? PK_CONV : PK_STRIDED, sizeof(T) == 8, L);
-  // a complex128 convolution too short to give every second compute unit a
-  // 16-column tile takes 8 columns (4 planes of 64^2: 4.2 against 5.2 us)
-  if (mode == 2 && sizeof(T) == 8 && v == 1 && tl_force_variant < 0 && (long)(a.nlines + 15) / 16 * planes < 128) v = 0;
+  LaunchSize own;
+  if (!sz) {
+    own.tiles = (long)(a.nlines + 15) / 16 * planes;
+    own.planes = planes;
+    own.bytes = (double)sizeof(cplx<T>) * a.nlines * (a.lin + a.lout) * planes;
+  }
+  const int v = tune_variant(mode == 2 ? PK_CONV : PK_STRIDED, sizeof(T) == 8, L, sz ? *sz : own);
   FWI_LENGTHS(launch_strided_v, L, v, a, planes, mode, st);
 }
 template <typename T>
@@ -1056,6 +1061,8 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
       return;
     }
   }
+  const LaunchSize conv_size = strided_size(g, B, PK_CONV, sizeof(cplx<T>));
+  const LaunchSize y_size = strided_size(g, B, PK_STRIDED, sizeof(cplx<T>));
   if (g.dim == 2) {
     // pass 2: columns along z, convolution, in place
     StridedArgs<T> s{};
@@ -1074,7 +1081,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
     s.lin = s.lout = g.nz;
     s.tile_major = conv_tile_major(g, sizeof(cplx<T>));
     prof_begin(KC_CONV + po, st);
-    strided_call<T>(g.Lz, s, B, 2, st);
+    strided_call<T>(g.Lz, s, B, 2, st, &conv_size);
     prof_end(KC_CONV + po, st, 2.0 * g.u1() * es, gbytes, masked, B);
   } else {
     // forward along y: U1 [b][z][ny][Lx] -> U2 [b][z][Ly][Lx]
@@ -1091,7 +1098,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
     s.lin = g.ny;
     s.lout = g.Ly;
     prof_begin(KC_Y_FWD + po, st);
-    strided_call<T>(g.Ly, s, (long)B * g.nz, 0, st);
+    strided_call<T>(g.Ly, s, (long)B * g.nz, 0, st, &y_size);
     prof_end(KC_Y_FWD + po, st, (double)(g.u1() + g.u2()) * es, 0.0, masked, B);
     // convolution along z, in place on U2
     StridedArgs<T> c{};
@@ -1110,7 +1117,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
     c.lin = c.lout = g.nz;
     c.tile_major = conv_tile_major(g, sizeof(cplx<T>));
     prof_begin(KC_CONV + po, st);
-    strided_call<T>(g.Lz, c, B, 2, st);
+    strided_call<T>(g.Lz, c, B, 2, st, &conv_size);
     prof_end(KC_CONV + po, st, 2.0 * g.u2() * es, gbytes, masked, B);
     // inverse along y with crop: U2 -> U1
     StridedArgs<T> v{};
@@ -1126,7 +1133,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
     v.lin = g.Ly;
     v.lout = g.ny;
     prof_begin(KC_Y_INV + po, st);
-    strided_call<T>(g.Ly, v, (long)B * g.nz, 1, st);
+    strided_call<T>(g.Ly, v, (long)B * g.nz, 1, st, &y_size);
     prof_end(KC_Y_INV + po, st, (double)(g.u1() + g.u2()) * es, 0.0, masked, B);
   }
   // last pass: rows along x, inverse, crop, epilogue

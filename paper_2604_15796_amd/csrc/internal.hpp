@@ -103,8 +103,6 @@ extern thread_local int tl_force_wide;     // 1: strided passes use 64-bit addre
 extern thread_local int tl_xy_off;         // 1: no fused lateral-elevation passes (separate x and y passes)
 // (Lx / 4, Ly / 2) of the grids built with fused lateral-elevation passes
 __host__ __device__ constexpr bool xy_shape(int MX, int HY) { return (MX == 64 && HY == 128) || (MX == 32 && HY == 64); }
-int default_variant(int pass, bool dbl, int L);
-int tune_variant(int pass, bool dbl, int L);
 int padded_length(int n);         // smallest ABI length >= 2n, 0 if none
 // smallest operator length >= 2n, 0 if none; the depth axis (the convolution's)
 // leaves out 216: its convolution takes 36 us where 256 takes 33 (128 planes of
@@ -140,6 +138,18 @@ struct Geo {
   long u1() const { return (long)nz * ny * Lx; }
   long u2() const { return dim == 3 ? (long)nz * Ly * Lx : 0; }
 };
+
+// What the built-in tile of a strided pass depends on besides the length
+// (default: a launch larger than every bound).
+struct LaunchSize {
+  long tiles = 1L << 40;   // workgroups with 16-column tiles
+  long planes = 1L << 40;
+  double bytes = 1e30;     // data that the operator's passes up to this one touch
+};
+LaunchSize strided_size(const Geo& g, int B, int pass, size_t es);
+// The built-in tile; tune_variant: the tuning table's where it has an entry
+int default_variant(int pass, bool dbl, int L, const LaunchSize& sz = LaunchSize());
+int tune_variant(int pass, bool dbl, int L, const LaunchSize& sz = LaunchSize());
 inline int xy_applies(const Geo& g) {
   return g.dim == 3 && !tl_xy_off && g.Lx % 4 == 0 && g.Ly % 2 == 0 && 2 * g.nx <= g.Lx && 2 * g.ny <= g.Ly &&
          xy_shape(g.Lx / 4, g.Ly / 2);

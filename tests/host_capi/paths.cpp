@@ -81,6 +81,31 @@ void launches(fwi_ctx*) {
   }
 }
 
+// The tile of a strided pass: by the launch's size where no table entry is, the
+// entry's at every size, and the tuner compares with the former.
+void tiles(fwi_ctx* ctx) {
+  using namespace fwi;
+  Geo g2{}, g3{};
+  g2.dim = 2, g2.nx = g2.nz = 64, g2.Lx = g2.Lz = 128, g2.ny = g2.Ly = 1;
+  g3.dim = 3, g3.nx = g3.ny = 128, g3.nz = 96, g3.Lx = g3.Ly = 256, g3.Lz = 192;
+  const size_t es = sizeof(c128);
+  auto conv = [&](int B) { return default_variant(PK_CONV, true, 128, strided_size(g2, B, PK_CONV, es)); };
+  auto elev = [&](int B) { return default_variant(PK_STRIDED, true, 256, strided_size(g3, B, PK_STRIDED, es)); };
+  expect(conv(4) == 0 && conv(16) == 0 && conv(64) == 0 && conv(1024) == 0 && conv(2048) == 1, "convolution");
+  expect(elev(1) == 0 && elev(2) == 1 + 1 && elev(32) == 2, "elevation");
+  FftTuning table;
+  tl_tune = &table;
+  table.v[PK_CONV][1][length_index(128)] = 1;
+  bool ok = true;
+  for (int B : {1, 16, 4096}) ok = ok && tune_variant(PK_CONV, true, 128, strided_size(g2, B, PK_CONV, es)) == 1;
+  tl_tune = nullptr;
+  expect(ok, "table entry at every size");
+  Prob small(64, 1, 64, 4, 1);
+  fwi_tune_report r{};
+  ok = fwi_autotune(ctx, &small.p, FWI_FP64, 4, 1, &r) == FWI_OK && r.default_variant[1] == 0;
+  expect(ok, "tuner's default on a short launch");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -89,6 +114,7 @@ int main(int argc, char** argv) {
   if (fwi_create(&ctx, 0, nullptr) != FWI_OK) return 1;
   if (what == "spectrum") spectrum(ctx);
   if (what == "launches") launches(ctx);
+  if (what == "tiles") tiles(ctx);
   fwi_destroy(ctx);
   if (emu::counts().violations) g_fail = 1;
   return g_fail;
