@@ -969,13 +969,12 @@ constexpr int kGradSeg = 16;
 // K-splits of the sampling / Jacobian GEMM over the n grid points. A split is
 // a serial chain of k steps, about 1.7 us each (a workgroup's 64 x 64 x 16
 // products at one compute unit's share of the FP64 matrix rate, or the load
-// latency where only a few 16-blocks are used), so small grids are cut to 64
-// points per split up to 96 splits (64^2 with 16 elements: 4 splits of 1024
-// took 160 us). From 131072 points on, one split per 1024 points: 64 while
-// the output tiles and frequencies already give >= 1024 workgroups, more (up
-// to 512) when they do not (a 3D grid with one frequency and 64 x 64 outputs
-// is one tile). Below that the count depends on n alone, so that a transmit
-// chunk sums its data in the same order as the whole frequency.
+// latency where only a few 16-blocks are used), so small grids are cut to
+// splits of 64 points (80 after rounding, see gemm_chunk), up to 96 of them
+// (64^2 with 16 elements: 4 splits of 1024 took 160 us). From 131072 points on,
+// one split per 1024 points: 64 while the output tiles and frequencies already
+// give >= 1024 workgroups, more (up to 512) when they do not (a 3D grid with one
+// frequency and 64 x 64 outputs is one tile). Below that see gemm_splits.
 // gemm_splits_max bounds every launch's count (buffer plans). A caller's
 // workspace that has no room for these partials is not refused while it holds
 // one split per 1024 points (gemm_splits_lean) and the call's other buffers:
@@ -992,12 +991,48 @@ int product_splits(const fwi_ctx* c, long n, size_t outs) {
   dry.take<c128>(outs * gemm_splits_max(n));
   return c->ws_ext && dry.used > c->ws_ext_bytes ? gemm_splits_lean(n) : gemm_splits_max(n);
 }
-// nks: the most that the buffer of the partials holds for the whole problem
-int gemm_splits(long n, int nf, int ni, int nj, int nks) {
-  if (n < 131072) return nks;
-  const long units = (long)nf * ((ni + 63) / 64) * ((nj + 63) / 64);
-  const long want = std::max<long>(64, (1024 + units - 1) / units);
-  return (int)std::min<long>(nks, want);
+// Splits of a sampling product of nf frequencies and ni transmits, part of the
+// problem's p->nf and nt (symmetric: sym). nks: the most that the buffer of the
+// partials holds for the whole problem.
+// Below 131072 points, the count with the least estimated time between one split
+// per 1024 points and the buffer's. The workgroups (splits x tiles x
+// frequencies) come in rounds of one per compute unit; a k step takes 0.25 +
+// 2.2 us per round with 64 x 64 products (0.4 + 0.15 + 0.128 b^2 with b < 4
+// blocks of 16; symmetric diagonal tiles 0.65 of it), a partial 4.5 ps per
+// output (fitted to timings of 84 products, most within 10%). More splits
+// shorten the chain as long as the last round is not nearly empty: J a of two
+// arrays, us at 96 splits (a fixed count) / as chosen: 65536 points, 3
+// frequencies, 33 elements 158 / 110; 6 frequencies, 64 elements, 30 transmits
+// 296 / 233; 8 frequencies, 64 elements, where 96 fills its rounds, 316 / 318;
+// 30000 points, 4 frequencies, 128 elements 315 / 287; 4096 points, 8
+// frequencies, 64 elements 58 / 53. The whole problem's tiles count, so that a
+// transmit chunk sums its data in the same order as the whole frequency.
+int gemm_splits(long n, int nf, int ni, const fwi_problem* p, int nt, int nks, bool sym = false) {
+  if (n >= 131072) {
+    const long units = (long)nf * ((ni + 63) / 64) * ((p->ne + 63) / 64);
+    const long want = std::max<long>(64, (1024 + units - 1) / units);
+    return (int)std::min<long>(nks, want);
+  }
+  const long ti = (nt + 63) / 64, tj = (p->ne + 63) / 64;
+  const int b = std::min(4, (std::max(nt, p->ne) + 15) / 16);
+  const double fixed = b < 4 ? 0.4 : 0.25, per_round = 0.15 + 0.128 * b * b;
+  auto estimate = [&](int s) {
+    const long chunk = gemm_chunk(n, s), r = (n + chunk - 1) / chunk;
+    auto step = [&](long tiles) { return fixed + per_round * (double)((r * p->nf * tiles + 255) / 256); };
+    double us = sym ? fixed + 0.65 * (step(ti) - fixed) : step(ti * tj);
+    if (sym && ti > 1) us += step(ti * (ti - 1) / 2);
+    return (double)(chunk / kGemmStep) * us + 4.5e-6 * (double)r * p->nf * nt * p->ne;
+  };
+  int best = (int)std::min<long>(nks, (n + 1023) / 1024);
+  double least = estimate(best);
+  for (int s = best + 1; s <= nks; ++s) {
+    const double us = estimate(s);
+    if (us < least) {
+      least = us;
+      best = s;
+    }
+  }
+  return best;
 }
 
 // Plans every buffer of an entry point; `entry` as in fwi_workspace_size.
@@ -1118,7 +1153,7 @@ struct Runner {
                        (long)ti * n, st);
         solve_rhs<T>(sb, l0, nf, ti, cb.S, F);
         launch_gemm_nt(nf, F, (long)ti * n, ti, cb.m64, P0g, (long)p->ne * n, p->ne, n, pc.coef + l0, cb.gpart,
-                       gemm_splits(n, nf, ti, p->ne, cb.nks), data_out + l0 * nd + (long)t0 * p->ne, st);
+                       gemm_splits(n, nf, ti, p, nt, cb.nks), data_out + l0 * nd + (long)t0 * p->ne, st);
         field_store(fields_out, off, (long)nf * ti * n);
       }
     }
@@ -1144,7 +1179,7 @@ struct Runner {
         launch_gemm_cn(nf, cb.wtx + rows, ti, p->ne, P0g, (long)p->ne * n, n, cb.S, (long)ti * n, st);
         solve_rhs<T>(sb, l0, nf, ti, cb.S, cb.fields);
         launch_gemm_nt(nf, cb.fields, (long)ti * n, ti, cb.m64, P0g, (long)p->ne * n, p->ne, n, pc.coef + l0,
-                       cb.gpart, gemm_splits(n, nf, ti, p->ne, cb.nks), data_out + rows, st);
+                       cb.gpart, gemm_splits(n, nf, ti, p, nt, cb.nks), data_out + rows, st);
         launch_residual((long)nf * ti * p->ne, data_out + rows, dobs + rows, cb.r + rows, cb.misfits + seg, st);
         launch_gemm_cn(nf, cb.r + rows, ti, p->ne, P0g, (long)p->ne * n, n, cb.S, (long)ti * n, st);
         solve_rhs<T>(sb, l0, nf, ti, cb.S, cb.lam);
@@ -1178,7 +1213,7 @@ struct Runner {
         c128* F = field_target(fields_out, off);
         solve_rhs<T>(sb, l0, nf, ni, pc.P0 + off, F);
         launch_gemm_nt(nf, F, (long)ni * n, ni, cb.m64, pc.P0 + (long)l0 * p->ne * n, (long)p->ne * n, p->ne, n,
-                       pc.coef + l0, cb.gpart, gemm_splits(n, nf, ni, p->ne, cb.nks), data_out + l0 * ne2 + (long)i0 * p->ne,
+                       pc.coef + l0, cb.gpart, gemm_splits(n, nf, ni, p, p->ne, cb.nks), data_out + l0 * ne2 + (long)i0 * p->ne,
                        st);
         field_store(fields_out, off, (long)nf * ni * n);
       }
@@ -1215,7 +1250,7 @@ struct Runner {
           rg = upstream + rows;
         } else {
           launch_gemm_nt(nf, F, (long)ni * n, ni, cb.m64, P0g, (long)p->ne * n, p->ne, n, pc.coef + l0, cb.gpart,
-                         gemm_splits(n, nf, ni, p->ne, cb.nks), data_out + rows, st);
+                         gemm_splits(n, nf, ni, p, p->ne, cb.nks), data_out + rows, st);
           launch_residual((long)nf * ni * p->ne, data_out + rows, dobs + rows, cb.r + rows, cb.misfits + seg, st);
           rg = cb.r + rows;
         }
@@ -1485,7 +1520,7 @@ void j_apply(fwi_ctx* c, const fwi_problem* p, const Geo& g, CallBufs& cb, int n
              const c128* a, c128* out) {
   const long n = g.n();
   launch_gemm_nt(p->nf, tx, (long)nt * n, nt, a, rx, (long)p->ne * n, p->ne, n, c->pc.coef, cb.gpart,
-                 gemm_splits(n, p->nf, nt, p->ne, cb.nks),
+                 gemm_splits(n, p->nf, nt, p, nt, cb.nks, tx == rx && nt == p->ne),
                  out, c->stream);
 }
 
@@ -1926,7 +1961,7 @@ int batch_impl(fwi_ctx* c, int ninst, const fwi_problem* probs, const double* co
       const int ne = I->p->ne, nf = I->p->nf;
       c128* data = I->data_out ? I->data_out : I->cb.data;
       launch_gemm_nt(nf, I->cb.fields, (long)ne * I->n, ne, I->cb.m64, I->pc->P0, (long)ne * I->n, ne, I->n,
-                     I->pc->coef, I->cb.gpart, gemm_splits(I->n, nf, ne, ne, I->cb.nks), data, main);
+                     I->pc->coef, I->cb.gpart, gemm_splits(I->n, nf, ne, I->p, ne, I->cb.nks), data, main);
       if (gradient) {
         launch_residual((long)nf * ne * ne, data, I->dobs, I->cb.r, I->cb.misfits, main);
         launch_gemm_cn(nf, I->cb.r, ne, ne, I->pc->P0, (long)ne * I->n, I->n, I->cb.S, (long)ne * I->n, main);
@@ -2517,7 +2552,7 @@ int fwi_jacobian_apply_tx(fwi_ctx* c, const fwi_problem* p, int nt, const void* 
     bind_workspace(c, ar, dry.used);
     c128* gpart = ar.take<c128>(part);
     launch_gemm_nt(p->nf, (const c128*)tx_fields, (long)nt * n, nt, (const c128*)a, (const c128*)rx_fields,
-                   (long)p->ne * n, p->ne, n, c->pc.coef, gpart, gemm_splits(n, p->nf, nt, p->ne, nks), (c128*)out,
+                   (long)p->ne * n, p->ne, n, c->pc.coef, gpart, gemm_splits(n, p->nf, nt, p, nt, nks, tx_fields == rx_fields && nt == p->ne), (c128*)out,
                    c->stream);
     FWI_HIP(hipStreamSynchronize(c->stream));
     return FWI_OK;

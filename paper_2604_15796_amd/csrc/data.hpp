@@ -5,7 +5,16 @@
 
 namespace fwi {
 
-// C[l][i][j] = coef[l] sum_n A[l][i][n] w[n] Bm[l][j][n]; part: [nks][nf][ni][nj] scratch.
+// Points per split of a sampling product cut into nks: whole k steps (256 bytes
+// of each row), and an odd number of them, so that the splits start on
+// different memory channels also where rows and splits are powers of two. With
+// short splits the rounding leaves fewer of them (64 of 64 points: 52 of 80).
+constexpr int kGemmStep = 16;
+inline long gemm_chunk(long n, int nks) {
+  return (((n + nks - 1) / nks + kGemmStep - 1) / kGemmStep | 1) * kGemmStep;
+}
+// C[l][i][j] = coef[l] sum_n A[l][i][n] w[n] Bm[l][j][n]; part: [nks][nf][ni][nj]
+// scratch, of which the splits that have points are used.
 // With w and one array as A and Bm the product is symmetric in (i, j), and one
 // triangle of it is computed.
 void launch_gemm_nt(int nf, const c128* A, long a_ls, int ni, const c128* w, const c128* Bm, long b_ls, int nj, long n,

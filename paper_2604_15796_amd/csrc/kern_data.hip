@@ -37,7 +37,7 @@ __device__ __forceinline__ void cmfma(c128 a, c128 b, v4d& cr, v4d& ci) {
 // four 16 x 16 complex tiles on the FP64 matrix cores; every A and Bm element
 // of a split is read from HBM once per output tile and staged through LDS.
 constexpr int GT = 64;  // output tile
-constexpr int GK = 16;  // k step
+constexpr int GK = kGemmStep;  // k step
 
 // part[ks][l][i][j] = sum over the split's k range of A[l][i][k] w[k] Bm[l][j][k]
 // NB: blocks of 16 rows and columns of the tile that are in use (4, or fewer
@@ -700,11 +700,8 @@ __global__ void k_copy_scalar(const double* __restrict__ in, double* __restrict_
 // ------------------------------------------------------------- launchers ---
 void launch_gemm_nt(int nf, const c128* A, long a_ls, int ni, const c128* w, const c128* Bm, long b_ls, int nj, long n,
                     const c128* coef, c128* part, int nks, c128* C, hipStream_t st) {
-  long kchunk = (n + nks - 1) / nks;
-  // whole k steps (256 bytes of each row), and an odd number of them, so that
-  // the splits start on different memory channels also where rows and splits
-  // are powers of two
-  kchunk = ((kchunk + GK - 1) / GK | 1) * GK;
+  const long kchunk = gemm_chunk(n, nks);
+  nks = (int)((n + kchunk - 1) / kchunk);
   const int tiles = ((ni + GT - 1) / GT) * ((nj + GT - 1) / GT);
   const int nb = (std::max(ni, nj) + 15) / 16;
   const long tot = (long)nf * ni * nj;

@@ -27,4 +27,6 @@ extern int iters_base, iters_spread;
 extern size_t mem_free;
 // hipMalloc calls so far; the calls that may still succeed (negative: all).
 extern long malloc_calls, malloc_left;
+// Splits that the last sampling product was launched with.
+extern int gemm_splits;
 }  // namespace emu

@@ -61,6 +61,7 @@ namespace emu {
 int iters_base = 12, iters_spread = 5;
 size_t mem_free = size_t(8) << 30;
 long malloc_calls = 0, malloc_left = -1;
+int gemm_splits = 0;
 static Counts g_counts;
 Counts& counts() { return g_counts; }
 void violation(const char* what) {

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "data.hpp"
 #include "emu.hpp"
 #include "fwi.h"
 #include "internal.hpp"
@@ -106,6 +107,40 @@ void tiles(fwi_ctx* ctx) {
   expect(ok, "tuner's default on a short launch");
 }
 
+// Splits of the sampling product: the matrix units' work of the fullest compute
+// unit (workgroups in rounds of 256, each a split's points) may not exceed that of
+// the coarsest count, one split per 1024 points, by more than 3%; a chunk
+// of the transmits has the splits of the whole problem.
+void splits(fwi_ctx* ctx) {
+  const int cases[][5] = {{256, 256, 3, 33, 33}, {64, 64, 4, 128, 128}, {96, 80, 8, 64, 64}, {150, 100, 5, 48, 21},
+                          {128, 64, 4, 128, 100}, {40, 30, 1, 7, 3}, {3, 2, 1, 1, 1}};
+  for (auto& k : cases) {
+    Prob q(k[0], 1, k[1], k[3], k[2]);
+    const int nf = k[2], ne = k[3], nt = k[4];
+    std::vector<cd> tx((size_t)nf * nt * q.n), rx((size_t)nf * ne * q.n), a(q.n), out((size_t)nf * nt * ne);
+    bool ok = fwi_jacobian_apply_tx(ctx, &q.p, nt, tx.data(), rx.data(), a.data(), out.data()) == FWI_OK;
+    auto rounds = [&](int s) {
+      const long chunk = fwi::gemm_chunk(q.n, s), r = (q.n + chunk - 1) / chunk;
+      return (double)chunk * (double)((r * nf * ((nt + 63) / 64) * ((ne + 63) / 64) + 255) / 256);
+    };
+    ok = ok && emu::gemm_splits >= 1 && rounds(emu::gemm_splits) <= 1.03 * rounds((int)((q.n + 1023) / 1024));
+    expect(ok, "splits fill their rounds");
+  }
+  Prob q(48, 1, 40, 20, 3);
+  std::vector<double> c(q.n, 1540.0);
+  std::vector<cd> data((size_t)3 * 20 * 20);
+  fwi_solve_opts o;
+  fwi_default_opts(&o);
+  int seen[3];
+  for (int k = 0; k < 3; ++k) {
+    o.max_rhs = k == 1 ? 20 : 0;
+    o.tx_chunk = k == 2 ? 7 : 0;
+    fwi_forward(ctx, &q.p, c.data(), nullptr, &o, data.data(), nullptr, nullptr);
+    seen[k] = emu::gemm_splits;
+  }
+  expect(seen[0] == seen[1] && seen[0] == seen[2], "one count for every chunk");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -115,6 +150,7 @@ int main(int argc, char** argv) {
   if (what == "spectrum") spectrum(ctx);
   if (what == "launches") launches(ctx);
   if (what == "tiles") tiles(ctx);
+  if (what == "splits") splits(ctx);
   fwi_destroy(ctx);
   if (emu::counts().violations) g_fail = 1;
   return g_fail;

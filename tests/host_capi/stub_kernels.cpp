@@ -447,6 +447,7 @@ void launch_check_complex(long n, const c128* x, int* out, hipStream_t st) {
 // ---------------------------------------------------------------- data ---
 void launch_gemm_nt(int nf, const c128* A, long a_ls, int ni, const c128* w, const c128* Bm, long b_ls, int nj, long n,
                     const c128* coef, c128* part, int nks, c128* C, hipStream_t st) {
+  emu::gemm_splits = nks;
   emu::submit(st, "gemm_nt", [=] {
     rd(A, 16 * ((nf - 1) * a_ls + (long)ni * n));
     rd(w, 16 * n);
