@@ -1867,7 +1867,6 @@ int batch_impl(fwi_ctx* c, int ninst, const fwi_problem* probs, const double* co
     I.grad = grad_out ? (c128*)grad_out[i] : nullptr;
     I.data_out = data_out ? (c128*)data_out[i] : nullptr;
     Arena dry;
-    I.cb.lean = c->ws_ext != nullptr;
     plan_call<T>(dry, I.p, o, FWI_ENTRY_GRADIENT, I.cb, I.sb);
     I.bytes = dry.used;
   }
@@ -1881,7 +1880,8 @@ int batch_impl(fwi_ctx* c, int ninst, const fwi_problem* probs, const double* co
   }
   // waves under a memory budget (60% of free device memory after the caches);
   // if the workspace still cannot be allocated, the budget is halved until
-  // every wave holds one instance
+  // every wave holds one instance. A caller's workspace that holds no wave of
+  // the full plans is tried with the lean ones (see gemm_splits_lean).
   size_t free_b = 0, total_b = 0;
   FWI_HIP(hipMemGetInfo(&free_b, &total_b));
   size_t budget = std::max<size_t>((size_t)(0.6 * (double)(free_b + c->ws_int_bytes)), 1);
@@ -1913,7 +1913,17 @@ int batch_impl(fwi_ctx* c, int ninst, const fwi_problem* probs, const double* co
       bind_workspace(c, a, maxw);
       break;
     } catch (const Error& e) {
-      if (e.code != FWI_E_NOMEM || c->ws_ext || maxn <= 1) throw;
+      if (e.code != FWI_E_NOMEM) throw;
+      if (c->ws_ext && !inst[0].cb.lean) {
+        for (BatchInst<T>& I : inst) {
+          Arena dry;
+          I.cb.lean = true;
+          plan_call<T>(dry, I.p, o, FWI_ENTRY_GRADIENT, I.cb, I.sb);
+          I.bytes = dry.used;
+        }
+        continue;
+      }
+      if (c->ws_ext || maxn <= 1) throw;
       budget = maxw / 2;
     }
   }

@@ -141,6 +141,40 @@ void splits(fwi_ctx* ctx) {
   expect(seen[0] == seen[1] && seen[0] == seen[2], "one count for every chunk");
 }
 
+// A batch in a caller's workspace: the splits of the call without one where they
+// fit, one per 1024 points in a smaller one, and NOMEM below that.
+void batch_workspace(fwi_ctx* ctx) {
+  Prob q(64, 1, 64, 64, 1);
+  std::vector<double> c(q.n, 1540.0);
+  std::vector<cd> d0(64 * 64), d1(64 * 64);
+  const fwi_problem probs[2] = {q.p, q.p};
+  const double* cs[2] = {c.data(), c.data()};
+  void* outs[2] = {d0.data(), d1.data()};
+  fwi_solve_opts o;
+  fwi_default_opts(&o);
+  o.restart = 8;
+  fwi_batch_stats st{};
+  auto run = [&](size_t bytes) {
+    std::vector<char> ws(bytes);
+    fwi_set_workspace(ctx, bytes ? ws.data() : nullptr, bytes);
+    const int rc = fwi_forward_batch(ctx, 2, probs, cs, nullptr, &o, outs, &st);
+    fwi_set_workspace(ctx, nullptr, 0);
+    return rc;
+  };
+  bool ok = run(0) == FWI_OK;
+  const int full = emu::gemm_splits;
+  size_t lo = 0, hi = size_t(256) << 20;  // the least workspace that is accepted
+  ok = ok && full > 4 && run(hi) == FWI_OK && emu::gemm_splits == full;
+  expect(ok, "ample workspace: the splits of the call without one");
+  while (hi - lo > 4096) {
+    const size_t mid = (lo + hi) / 2;
+    (run(mid) == FWI_OK ? hi : lo) = mid;
+  }
+  ok = run(hi) == FWI_OK && emu::gemm_splits < full;
+  expect(ok, "least workspace: fewer splits");
+  expect(run(lo) == FWI_E_NOMEM, "below it: refused");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -151,6 +185,7 @@ int main(int argc, char** argv) {
   if (what == "launches") launches(ctx);
   if (what == "tiles") tiles(ctx);
   if (what == "splits") splits(ctx);
+  if (what == "batch") batch_workspace(ctx);
   fwi_destroy(ctx);
   if (emu::counts().violations) g_fail = 1;
   return g_fail;
