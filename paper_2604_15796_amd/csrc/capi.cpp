@@ -763,10 +763,11 @@ struct ArnoldiDriver {
   }
   // The sum of the parts costs a launch of its own (3 to 5 us, its result is
   // waited for) or 16 bytes per part and vector in every workgroup of the
-  // orthogonalising pass. The latter while the parts are few against the pass's
-  // 2048 points per vector and the launch is short (plane waves 192x160, 3360
-  // workgroups: 1.2% of the gradient; 256^2, 512 right-hand sides: the launch is
-  // 5 us of 800 per step, less than the workgroups' sums).
+  // orthogonalising pass. The latter while the launch is short: whole solves with
+  // the sums in the pass against the separate kernel, 32^2 to 256^2 and 3D, at
+  // 1024, 2048, 4096, 8192 and 16384 parts in all: complex64 +2.3 to 3.5%, +0.8 to
+  // 2.2%, 0 to +0.5%, -0.4 to -0.8%, -0.7 to -1.1%; complex128 +0.7 to 1.5%, +1%, 0
+  // to +0.5%, 0 to +0.4%, the same. At most 64 parts per RHS (the most timed).
   // Only with the built-in row tile: the larger ones have no registers to spare.
   bool fuse_hsum(int parts) const {
     return !g.xy && parts <= 64 && (long)parts * ks.B <= 4096 &&
