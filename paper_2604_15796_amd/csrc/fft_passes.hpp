@@ -47,8 +47,6 @@ __device__ __forceinline__ bool any_row(const int* s_ok, int nl) {
   return any != 0;
 }
 
-constexpr int kMaxDotVec = 33;  // basis vectors of the largest restart (32) + 1
-
 // ------------------------------------------------------------- row pass 1 ---
 // Input of the first pass: the rows of x as they are, or a combination with
 // basis vectors formed first (see k_row_fwd).
@@ -999,7 +997,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
       xa.y = y;
       if (dots) {
         dots->nparts = 0;
-        if (epi == EPI_VIE && g.nz <= kMaxDotParts && dots->nvec <= kMaxDotVec) {
+        if (epi == EPI_VIE && fused_dot_parts(g.nz, 1, dots->nvec)) {
           epi = EPI_VIE_DOT;
           xa.dbasis = static_cast<const cplx<T>*>(dots->basis);
           xa.dvs = dots->vs;
@@ -1111,10 +1109,8 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
   if (dots) {
     dots->nparts = 0;
     const int nl = row_inv_nl<T>(g.Lx);
-    // (grids of fewer rows than a workgroup holds keep their rows packed)
-    const long parts = (rows_per_rhs + nl - 1) / nl;
-    if (epi == EPI_VIE && (rows_per_rhs >= nl || rows_per_rhs % nl == 0) && parts <= kMaxDotParts &&
-        dots->nvec <= kMaxDotVec) {
+    const int parts = fused_dot_parts(rows_per_rhs, nl, dots->nvec);
+    if (epi == EPI_VIE && parts) {
       epi = EPI_VIE_DOT;
       r.basis = static_cast<const cplx<T>*>(dots->basis);
       r.vs = dots->vs;
@@ -1123,7 +1119,7 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
       r.B = B;
       r.dotp = dots->dotp;
       r.dstride = dots->dstride;
-      dots->nparts = (int)parts;
+      dots->nparts = parts;
     }
   }
   // per RHS: the x-pass intermediate, then x and y (VIE), or x, rhs, the

@@ -10,12 +10,15 @@ constexpr int NT = 256;
 constexpr int kLdsMax = 160 * 1024;
 
 // rows per workgroup of variant v: 2048 / 4096 / 8192 points
+__host__ __device__ constexpr int row_lines(int L, int v, int es) {
+  const int pts = v == 0 ? 2048 : v == 1 ? 4096 : 8192;
+  const int nl0 = pts / L > 1 ? pts / L : 1;
+  // keep the workgroup inside the LDS budget
+  return nl0 * (L + L / 8) * es <= kLdsMax - 4096 ? nl0 : (nl0 / 2 > 0 ? nl0 / 2 : 1);
+}
 template <typename T, int L, int V>
 __host__ __device__ constexpr int row_nl() {
-  constexpr int pts = V == 0 ? 2048 : V == 1 ? 4096 : 8192;
-  constexpr int nl0 = pts / L > 1 ? pts / L : 1;
-  // keep the workgroup inside the LDS budget
-  return nl0 * (L + L / 8) * (int)sizeof(cplx<T>) <= kLdsMax - 4096 ? nl0 : (nl0 / 2 > 0 ? nl0 / 2 : 1);
+  return row_lines(L, V, (int)sizeof(cplx<T>));
 }
 // strided-pass variants: (columns, threads) = (8, 256), (16, 256), (16, 512),
 // with 32 columns instead of 16 for complex64 lines of length 256 (256-byte

@@ -159,10 +159,17 @@ enum Epilogue { EPI_VIE = 0, EPI_RESID = 1, EPI_COPY = 2, EPI_RESID32 = 3, EPI_V
 
 // Arnoldi inner products fused into the last pass of an EPI_VIE operator:
 // dotp[b][part][i] = vscale_i,b * sum over the part's rows of conj(V_i) . y,
-// i < nvec, one part per workgroup of the inverse row pass. Done only when a
+// i < nvec, one part per workgroup of the inverse row pass (the last of a RHS
+// may hold fewer rows). Done only when a
 // RHS fills a workgroup's rows at least once and there are at most kMaxDotParts
 // parts per RHS; launch_vie reports whether it did them (and `nparts`).
 constexpr int kMaxDotParts = 2048;
+constexpr int kMaxDotVec = 33;  // basis vectors of the largest restart (32) + 1
+// the parts of a RHS of `rows` rows in workgroups of nl; 0: not fused
+constexpr int fused_dot_parts(long rows, int nl, int nvec) {
+  const long parts = (rows + nl - 1) / nl;
+  return rows >= nl && parts <= kMaxDotParts && nvec <= kMaxDotVec ? (int)parts : 0;
+}
 struct VieDots {
   const void* basis = nullptr;   // V_0 [B][n] (cplx<T>), vector i at basis + i*vs
   long vs = 0;

@@ -27,6 +27,8 @@ extern int iters_base, iters_spread;
 extern size_t mem_free;
 // hipMalloc calls so far; the calls that may still succeed (negative: all).
 extern long malloc_calls, malloc_left;
+// Launches so far of the stand-in kernel of that name.
+long launches(const char* name);
 // Splits that the last sampling product was launched with.
 extern int gemm_splits;
 }  // namespace emu

@@ -19,6 +19,7 @@
 #include <cstring>
 #include <map>
 #include <set>
+#include <string>
 #include <vector>
 
 #include "emu.hpp"
@@ -104,7 +105,12 @@ void enqueue(EmuStream* s, const char* name, bool kernel, std::function<void()> 
 }  // namespace
 
 namespace emu {
-void submit(hipStream_t st, const char* name, std::function<void()> body) { enqueue(S(st), name, true, std::move(body)); }
+static std::map<std::string, long> g_launches;
+long launches(const char* name) { return g_launches[name]; }
+void submit(hipStream_t st, const char* name, std::function<void()> body) {
+  g_launches[name] += 1;
+  enqueue(S(st), name, true, std::move(body));
+}
 void rd(const void* p, size_t bytes) {
   if (!bytes) return;
   if (!p) {

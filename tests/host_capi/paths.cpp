@@ -1,6 +1,7 @@
 // Single calls of the C ABI on the host stand-in (see driver.cpp), each a
 // condition that the call sequences there do not set up. Prints "ok <name>" per
 // check; run under the sanitizers.
+#include <algorithm>
 #include <complex>
 #include <cstdio>
 #include <cstdlib>
@@ -175,6 +176,48 @@ void batch_workspace(fwi_ctx* ctx) {
   expect(run(lo) == FWI_E_NOMEM, "below it: refused");
 }
 
+// Where the coefficients of an Arnoldi step are summed: in the orthogonalising
+// pass on short launches with the built-in row tile, else in a kernel of its own,
+// one launch per step; and where the inner products are a kernel of their own.
+void sums(fwi_ctx* ctx) {
+  signed char none[88], wide[88];
+  std::fill(none, none + 88, (signed char)-1);
+  std::copy(none, none + 88, wide);
+  for (int d = 0; d < 2; ++d)
+    for (int l = 0; l < 11; ++l) wide[(fwi::PK_ROW_FWD * 2 + d) * 11 + l] = 1;
+  struct {
+    Prob q;
+    const signed char* table;
+    bool own_sum, own_dots;
+  } cases[] = {{Prob(37, 1, 70, 5, 2), none, false, false},    // ragged last part
+               {Prob(37, 1, 37, 5, 2), wide, false, false},    // length 80 has no tuned tile
+               {Prob(64, 1, 50, 5, 2), wide, true, false},     // tuned row tile
+               {Prob(16, 20, 210, 2, 1), none, true, false},   // 66 parts
+               {Prob(120, 1, 130, 61, 4), none, true, false},  // 17 parts, 244 right-hand sides
+               {Prob(20, 1, 13, 3, 1), none, false, true}};    // fewer rows than a workgroup's
+  for (auto& k : cases) {
+    fwi_set_tuning(ctx, k.table, 88);
+    std::vector<double> c(k.q.n, 1540.0);
+    std::vector<cd> data((size_t)k.q.p.nf * k.q.p.ne * k.q.p.ne);
+    bool ok = true;
+    for (int prec = 0; prec < 2; ++prec) {
+      fwi_solve_opts o;
+      fwi_default_opts(&o);
+      o.restart = 8;
+      o.precision = prec;
+      const long s0 = emu::launches("hsum"), d0 = emu::launches("dots"), g0 = emu::launches("givens");
+      ok = ok && fwi_forward(ctx, &k.q.p, c.data(), nullptr, &o, data.data(), nullptr, nullptr) == FWI_OK;
+      const long steps = emu::launches("givens") - g0;
+      ok = ok && steps > 0;
+      // (a step enqueued after the last right-hand side stopped may lack its rotations)
+      const long s = emu::launches("hsum") - s0, d = emu::launches("dots") - d0;
+      ok = ok && (k.own_sum ? s >= steps : s == 0) && (k.own_dots ? d >= steps : d == 0);
+    }
+    expect(ok, "sums");
+  }
+  fwi_set_tuning(ctx, nullptr, 0);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -185,6 +228,7 @@ int main(int argc, char** argv) {
   if (what == "launches") launches(ctx);
   if (what == "tiles") tiles(ctx);
   if (what == "splits") splits(ctx);
+  if (what == "sums") sums(ctx);
   if (what == "batch") batch_workspace(ctx);
   fwi_destroy(ctx);
   if (emu::counts().violations) g_fail = 1;

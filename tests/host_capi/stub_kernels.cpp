@@ -10,6 +10,7 @@
 
 #include "data.hpp"
 #include "emu.hpp"
+#include "fft_tiles.hpp"
 #include "internal.hpp"
 #include "krylov.hpp"
 
@@ -63,6 +64,7 @@ void krylov_cycle_init(const KrylovState<T>& s, int first, double, double, hipSt
     k.counters[0] = act;
     k.counters[1] = act;
     k.maxrel[0] = act ? 1e-3 : 1e-9;
+    k.arrive[0] = 0;
   });
 }
 
@@ -86,7 +88,6 @@ void krylov_hsum(const KrylovState<T>& s, int j, int ndot, hipStream_t st) {
     rd(k.dotp, sizeof(c128) * k.B * ndot * (k.JM + 1));
     rd(k.H, sizeof(c128) * k.B * (k.JM + 1) * k.JM);
     wr(k.hcoef, sizeof(c128) * k.B * (k.JM + 1));
-    k.counters[0] = 0;
   });
 }
 
@@ -100,6 +101,7 @@ void krylov_givens(const KrylovState<T>& s, int j, const double* rowpart, int ro
     rd(k.sn, sizeof(c128) * k.B * k.JM);
     rd(k.gv, sizeof(c128) * k.B * (k.JM + 1));
     rd(k.target, sizeof(double) * k.B);
+    if (k.arrive[0] != 0) emu::violation("workgroups of an earlier launch left in the arrival counter");
     int act = 0;
     for (int b = 0; b < k.B; ++b) {
       if (!k.active[b]) continue;
@@ -112,6 +114,7 @@ void krylov_givens(const KrylovState<T>& s, int j, const double* rowpart, int ro
         ++act;
       }
     }
+    k.arrive[0] = 0;  // by the last workgroup
     k.counters[0] = act;
   });
 }
@@ -192,15 +195,10 @@ void launch_copy_c128(long count, const c128* in, c128* out, hipStream_t st) {
 }
 
 // ------------------------------------------------------------ operator ---
-// Rows per workgroup of the inverse row pass (the launcher fuses the Arnoldi
-// inner products only when a workgroup's rows belong to one RHS).
+// Rows per workgroup of a row pass.
 template <typename T>
-static int row_inv_rows(int L) {
-  const int v = tune_variant(PK_ROW_INV, sizeof(T) == 8, L);
-  const int pts = v == 0 ? 2048 : v == 1 ? 4096 : 8192;
-  int nl = std::max(pts / L, 1);
-  if (nl * (L + L / 8) * (int)sizeof(cplx<T>) > 160 * 1024 - 4096) nl = std::max(nl / 2, 1);
-  return nl;
+static int rows_per_workgroup(int pass, int L) {
+  return row_lines(L, tune_variant(pass, sizeof(T) == 8, L), (int)sizeof(cplx<T>));
 }
 
 template <typename T>
@@ -226,6 +224,8 @@ void launch_vie_rows(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
   const long u2 = g.u2();
   if (has_xu && (sizeof(T) != 8 || active)) throw Error(-6, "the fused solution update is for complex128 residuals");
   if (has_start && (!m || active)) throw Error(-6, "the start pass needs the contrast and every RHS");
+  if (ov.ndot && (xy || ov.nvec > kMaxDotVec || rows_per_workgroup<T>(PK_ROW_FWD, g.Lx) != row_lines(g.Lx, 0, (int)e)))
+    throw Error(-6, "the coefficient sum needs the built-in row tile of the separate passes");
   emu::submit(st, "row_fwd", [=] {
     if (active) rd(active, sizeof(int) * B);
     bool transform = true;
@@ -240,7 +240,15 @@ void launch_vie_rows(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
       wr(const_cast<cplx<T>*>(x), e * B * n);
     } else if (has_orth) {
       for (int i = 0; i < ov.nvec; ++i) rd((const char*)ov.basis + (size_t)i * ov.vs * e, e * B * n);
-      rd(ov.coef, sizeof(c128) * B * ov.cstride);
+      if (ov.ndot) {  // the coefficients from the parts, column nvec - 1 of H
+        rd(ov.dotp, sizeof(c128) * B * ov.ndot * ov.cstride);
+        rd(ov.vscale, e * B * ov.nvec);
+        for (long b = 0; b < B; ++b)
+          for (int i = 0; i < ov.nvec; ++i)
+            wr(ov.H + (b * ov.cstride + i) * (ov.cstride - 1) + ov.nvec - 1, sizeof(c128));
+      } else {
+        rd(ov.coef, sizeof(c128) * B * ov.cstride);
+      }
       rd(x, e * B * n);
       wr(const_cast<cplx<T>*>(x), e * B * n);
       wr(ov.rowpart, sizeof(double) * B * rows);
@@ -279,16 +287,9 @@ void launch_vie_tail(const Geo& g, const Twiddles& tw, int B, const cplx<T>* x, 
   }
   if (dots) {
     dots->nparts = 0;
-    const int nl = row_inv_rows<T>(g.Lx);
-    if (xy) {
-      if (epi == EPI_VIE && g.nz <= kMaxDotParts && dots->nvec <= 33) {
-        dots->nparts = g.nz;
-        dv = *dots;
-      }
-    } else if (epi == EPI_VIE && rows % nl == 0 && rows / nl <= kMaxDotParts && dots->nvec <= 33) {
-      dots->nparts = (int)(rows / nl);
-      dv = *dots;
-    }
+    const int nl = xy ? 1 : rows_per_workgroup<T>(PK_ROW_INV, g.Lx);
+    if (epi == EPI_VIE) dots->nparts = fused_dot_parts(xy ? g.nz : rows, nl, dots->nvec);
+    if (dots->nparts) dv = *dots;
   }
   const bool fused = dv.nparts > 0;
   emu::submit(st, "vie_tail", [=] {

@@ -37,7 +37,7 @@ def paths(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name,checks", [("spectrum", 4), ("launches", 6), ("tiles", 4), ("splits", 8),
-                                         ("batch", 3)])
+                                         ("batch", 3), ("sums", 6)])
 def test_host_path(paths, name, checks):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     p = subprocess.run([str(paths), name], capture_output=True, text=True, timeout=600, env=env)
