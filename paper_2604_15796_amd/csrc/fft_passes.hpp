@@ -346,16 +346,19 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
     for (int i = threadIdx.x; i < C::NL * NsL; i += NT) s_part[i] = 0.0;
   // with inner products a workgroup's rows belong to one RHS (nparts per RHS,
   // the last one ragged); else rows are packed across RHS
+  constexpr bool DOT = EPI == EPI_VIE_DOT;
   long g0 = (long)blockIdx.x * C::NL, gend = a.nrows;
-  if constexpr (EPI == EPI_VIE_DOT) {
-    const unsigned b = blockIdx.x / (unsigned)a.nparts, part = blockIdx.x % (unsigned)a.nparts;
-    g0 = (long)b * a.rows_per_rhs + (long)part * C::NL;
-    gend = (long)(b + 1) * a.rows_per_rhs;
+  unsigned dot_b = 0, dot_part = 0;
+  if constexpr (DOT) {
+    dot_b = blockIdx.x / (unsigned)a.nparts;
+    dot_part = blockIdx.x - dot_b * (unsigned)a.nparts;
+    g0 = (long)dot_b * a.rows_per_rhs + (long)dot_part * C::NL;
+    gend = (long)(dot_b + 1) * a.rows_per_rhs;
   }
   for (int l = threadIdx.x; l < C::NL; l += NT) {
     const long g = g0 + l;
     int ok = g < gend;
-    const long b = ok ? g / a.rows_per_rhs : 0;
+    const long b = DOT ? (long)dot_b : ok ? g / a.rows_per_rhs : 0;
     if (ok && a.active && !a.active[b]) ok = 0;
     s_ok[l] = ok;
     s_s[l] = a.scale ? a.scale[b] : mk((T)1, (T)0);
@@ -370,7 +373,7 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
     const int p = pb + ro;
     const bool st = s_ok[line] && p < a.nout;
     const long o = row(line) * a.nout + (p < a.nout ? p : a.nout - 1);
-    if constexpr (EPI == EPI_VIE || EPI == EPI_VIE_DOT) {
+    if constexpr (EPI == EPI_VIE || DOT) {
       const cplx<T> y = (a.x[o] - v) * s_s[line];  // the operator is linear: s (x - conv(m x))
       if (st) a.y[o] = y;
     } else if constexpr (RESID) {
@@ -393,15 +396,13 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
       a.rowpart[g0 + threadIdx.x] = s;
     }
   }
-  if constexpr (EPI == EPI_VIE_DOT) {
+  if constexpr (DOT) {
     // The workgroup's rows (one RHS, contiguous in y and in every basis
     // vector) were just stored; after the barrier each thread reads back EPD
     // elements of them and streams the basis vectors over the same elements
     // (two or four vectors at a time cost registers: 1.5% of a 256^2 gradient).
     __syncthreads();
     constexpr int EPD = (C::NL * (L / 2) + NT - 1) / NT;
-    const long b0 = g0 / a.rows_per_rhs;
-    const int part = (int)((g0 - b0 * a.rows_per_rhs) / C::NL);
     const long base = g0 * a.nout;
     const int cnt = (int)(gend - g0 < C::NL ? gend - g0 : C::NL) * a.nout;
     const int t = threadIdx.x;
@@ -447,8 +448,8 @@ __global__ void __launch_bounds__(NT) k_row_inv(RowInvArgs<T> a) {
         r += red[0][t][w];
         m += red[1][t][w];
       }
-      const double sc = (double)a.vscale[(long)t * a.B + b0].x;  // stored V_i = basis vector / sc
-      a.dotp[((long)b0 * a.nparts + part) * a.dstride + t] = mk(sc * r, sc * m);
+      const double sc = (double)a.vscale[(long)t * a.B + dot_b].x;  // stored V_i = basis vector / sc
+      a.dotp[(long)blockIdx.x * a.dstride + t] = mk(sc * r, sc * m);
     }
   }
 }
