@@ -350,7 +350,7 @@ struct fwi_ctx {
   std::vector<hipStream_t> branch;             // one per instance of a wave (default priority)
   std::vector<hipEvent_t> branch_ev;
   hipEvent_t fork_ev = nullptr;
-  hipEvent_t count_ev = nullptr;               // active-count copy of the solver loop
+  hipEvent_t count_ev = nullptr;               // the solver loop's active count is written
   unsigned long long* d_itstat = nullptr;      // iteration max / sum of the current call's solves
   char* scratch_dev = nullptr;                 // this device's copy of `scratch`
   ~fwi_ctx() {
@@ -660,7 +660,7 @@ void plan_solve(Arena& a, const Geo& g, int B, int JM, SolveBufs<T>& s) {
   k.active = a.take<int>(B);
   k.ncol = a.take<int>(B);
   k.iters = a.take<int>(B);
-  k.counters = a.take<int>(6);  // active counts, then the max relative residual: one copy reads both
+  k.counters = a.take<int>(6);  // active counts, the max relative residual, the arrivals (8-byte aligned)
   k.maxrel = k.counters ? reinterpret_cast<double*>(k.counters + 2) : nullptr;
   k.arrive = k.counters ? reinterpret_cast<unsigned long long*>(k.counters + 4) : nullptr;
   s.rowpart = a.take<double>((size_t)B * g.nz * g.ny);

@@ -133,8 +133,8 @@ __global__ void __launch_bounds__(256, 3) k_gemm_nt(const c128* __restrict__ A, 
 // and {w, w + 1} (mod 4) for every k step and half of the k steps of pair
 // {w mod 2, w mod 2 + 2}: 2.5 of the 4 block products per wave of the general
 // tile, the same for all waves, and each field element is fetched once. Bound
-// by the FP64 matrix cores, as the general product is: 209 us at 256^2, 8
-// frequencies, 64 elements, against 327 (both kinds of tile in one kernel need
+// by the FP64 matrix cores, as the general product is: 218 us at 256^2, 8
+// frequencies, 64 elements, against 322 (both kinds of tile in one kernel need
 // 266 registers, one workgroup per compute unit: 300 us).
 template <int NB>
 __global__ void __launch_bounds__(256, 3) k_gemm_sym(const c128* __restrict__ F, long f_ls, int ni,
@@ -395,8 +395,8 @@ __global__ void __launch_bounds__(256) k_gemm_cn(const c128* __restrict__ M, int
 // (mod 4) and, for c >= 2, c - 2 (10 of the 16 block products). A wave owns 16
 // grid points and every row block, so the pairs are compile-time and equal
 // for all waves, and the sum over the rows stays inside the wave. Bound by the
-// FP64 matrix cores: 285 us at 256^2, 8 frequencies, 64 elements, against 431
-// for k_gemm_cn<true>; 0.66 against 1.09 ms per 3 frequencies of 384^2 with
+// FP64 matrix cores: 294 us at 256^2, 8 frequencies, 64 elements, against 426
+// for k_gemm_cn<true>; 0.68 against 1.09 ms per 3 frequencies of 384^2 with
 // 128 elements. part [nf][row tiles][n] as in k_gemm_cn<true>.
 template <int NB>
 __global__ void __launch_bounds__(256) k_gemm_cn_sym(const c128* __restrict__ M, int ni, const c128* __restrict__ P,
@@ -435,7 +435,7 @@ __global__ void __launch_bounds__(256) k_gemm_cn_sym(const c128* __restrict__ M,
       rp[q] = Pl[(long)(j < ni ? j : ni - 1) * n + (nn < n ? nn : n - 1)];
     }
   };
-  // D: the tile's distance from the diagonal tile's column block CB (compile time)
+  // one step of CK columns
   auto step = [&](int jb, auto cb_tag, bool last) {
     constexpr int CB = decltype(cb_tag)::value;  // column block of the diagonal tile, or -1 past it
 #pragma unroll
@@ -664,7 +664,7 @@ __global__ void __launch_bounds__(256) k_dot_re_partial(long n, const c128* __re
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 // One workgroup, a fixed order (one thread summing 512 partials one after
-// another took 33 us, 23 times per ADMM iteration; 4 us now).
+// another took 33 us, 23 times per ADMM iteration; 4.7 us now).
 __global__ void __launch_bounds__(256) k_sum_partial(int nb, const double* __restrict__ part,
                                                      double* __restrict__ out) {
   __shared__ double red[4];

@@ -121,11 +121,13 @@ __global__ void __launch_bounds__(KT) k_hsum(int j, int B, const int* __restrict
 // Bound by latency, not by bytes: the column and the earlier rotations are
 // fetched by all threads at once into LDS while the row sums are loaded, so
 // the serial rotations run from LDS (each fetched them from memory in turn
-// before: 4.5 us at 13 columns of 64^2, 9.5 at 20; now 3.8 and 6). The
-// count of active RHS and of workgroups arrived share one 64-bit atomic, so
-// the last workgroup knows the total without a fence and writes it straight
-// to counters[0] (pinned host memory in the solver loop, where it replaces a
-// 2-4 us copy per step).
+// before). The count of active RHS and of workgroups arrived share one 64-bit
+// atomic, so the last workgroup knows the total without a fence and writes it
+// straight to counters[0] (pinned host memory in the solver loop, where it
+// replaces a copy per step). us per launch before, with the copy / now, means
+// over a gradient: 16 RHS of 64^2 4.4 + 1.9 / 4.6; 99 RHS of 200x150 (up to 20
+// columns) 9.5 + 4.0 / 6.3; 105 RHS of 192x160 5.2 + 3.8 / 5.0; 512 RHS of 256^2,
+// whose arrivals queue at the one counter, 9.8 + 4.1 / 10.6.
 __device__ __forceinline__ void givens_arrive(int act, unsigned long long* arrive, int* counters) {
   const unsigned long long old = atomicAdd(arrive, (1ULL << 32) | (unsigned)act);
   if ((unsigned)(old >> 32) == gridDim.x - 1) {
@@ -281,7 +283,7 @@ __global__ void __launch_bounds__(1024) k_cycle_init(int B, int nblk, int first,
 // Back-substitution R y = g for each RHS (k = ncol columns), one wave per RHS:
 // the triangle is fetched at once into LDS, then column by column lane r
 // subtracts R[r][i] y_i (one thread per RHS reading the triangle from memory
-// entry by entry took 18 us at 14 columns and 57 at 20).
+// entry by entry took 19 us at 14 columns of 64^2; 6.5 now).
 template <typename T, int JM>
 __global__ void __launch_bounds__(64) k_backsolve(int B, const int* __restrict__ ncol, const c128* __restrict__ H,
                                                   const c128* __restrict__ gv, c128* __restrict__ y,
