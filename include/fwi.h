@@ -419,8 +419,9 @@ int fwi_profile_read(const fwi_ctx* ctx, int cls, double* total_ms, long long* l
  * variant of every pass on the device for this problem's grid with B
  * right-hand sides (reps launches each, HIP events) and stores the fastest per
  * (pass, precision, padded length) in the context; a variant replaces the
- * built-in default only if it is at least 2% faster. Lengths that are not of
- * fwi_padded_length have one tile per pass and no entry. Later calls use the
+ * built-in tile of this launch (complex128 strided passes: chosen by its size)
+ * only if it is at least 2% faster. Lengths that are not of fwi_padded_length
+ * have one tile per pass and no entry. Later calls of any size use the
  * table. Report rows: 0 row forward, 1 convolution, 2 row inverse, 3 / 4
  * elevation forward / inverse (3D, tuned on their summed time). */
 typedef struct fwi_tune_report {
